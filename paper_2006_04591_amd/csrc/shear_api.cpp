@@ -1176,8 +1176,9 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     const int K = s->K, N = s->rows, M = s->cols;
     const int cpo = shear::shrink_cinp(K), c3 = shear::shrink_coutp(K);
     const size_t pix = (size_t)batch * N * M;
-    const int ntiles = (int)(pix / (8 * 32));
-    const int G = std::max(1, std::min(ntiles, 2 * std::max(1, s->cus)));
+    // weight-gradient blocks: two per compute unit, a multiple of the 8 XCDs, at most one per 8 x 32 pixels
+    // (rows % 16 == 0 and cols % 128 == 0: at least 8 such tiles)
+    const int G = (int)std::min<size_t>(pix / (8 * 32), 2 * (size_t)std::max(4, s->cus)) / 8 * 8;
     const size_t part_stride = (size_t)std::max({32 * 9 * cpo + 32, c3 * 9 * 32 + c3, 32 * 9 * 32 + 32});
     // workspace: scale | h1 | h2 | d o | dh2 | dh1 | transposed W3 | transposed W2 | partials
     size_t off = 0;

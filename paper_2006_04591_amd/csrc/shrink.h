@@ -65,7 +65,7 @@ hipError_t launch_pack_z(const float* c, const float* scale, unsigned short* z, 
 // gradient channels; 5: backward data from shrink_cinp(K) gradient channels; 6: layer 0 with its input
 // staged straight from the FP32 coefficients (coef, scale, cin = K) instead of the packed z.
 hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream_t st);
-// weight gradients of layer 0, 1 or 2 (partials of `blocks` blocks of 32-pixel x 8-row tiles)
+// weight gradients of layer 0, 1 or 2 (partials of `blocks` blocks, a multiple of 8; N % 8 == 0, M % 32 == 0)
 hipError_t launch_wgrad(int layer, int K, const WgradArgs& a, int blocks, hipStream_t st);
 hipError_t launch_wgrad_reduce(const float* part, float* dW, float* db, int nblk, int cout, int cin, int coutp, int cinp,
                                hipStream_t st);

@@ -927,124 +927,212 @@ __global__ __launch_bounds__(PTHREADS, 2) void k_conv_shrink(ConvArgs a, int nti
 
 // ---------------------------------------------------------------- weight gradients
 // dW[co][tap][ci] = sum over pixels p of dy[co](p) x[ci](p + tap offset): an MFMA GEMM with
-// M = output channels, N = (tap, input channel), K = pixels (one 32-pixel tile row per step).
-// A block loops over pixel tiles (stride gridDim.x) and writes its partial sums, and the bias
-// gradient sum_p dy[co](p), to part[blockIdx.x]; k_wgrad_reduce adds the partials in block order.
-// x: bf16 channel-last with CINP channels (the packed z, or a hidden activation).
-// Rows of the staged input tile have a pitch of XP = 40 bf16 (80 bytes): 16-byte aligned, so a
-// lane's 8 pixels at a tap's column offset come from two aligned 16-byte reads and a byte-align.
-constexpr int XP = 40;
+// M = output channels, N = (tap, input channel), K = pixels. Both operands are channel-last in
+// memory and in LDS, so a lane's 8 pixels of one channel are a column of the staged tile; the
+// gfx950 transposing LDS read (ds_read_b64_tr_b16: each group of 16 lanes reads 4 pixels x 16
+// channels, 8 bytes a lane, and receives one channel's 4 pixels a lane) delivers them without a
+// transposed copy, and a tap's column offset is an address offset. Staging is then plain 16-byte
+// copies. At 16 x 512^2 x 49 the three layers (64 x 32, 32 x 64 and 32 x 32 channels) take 180, 187
+// and 120 us, 4.5 TB/s of operands; staged channel-major with 2-byte copies they took 1320, 1108
+// and 723 us.
+//
+// A block walks units of a 32-pixel column strip by R rows, 4 rows (a chunk) at a time. Row yy of x
+// meets the dy rows yy + 1, yy, yy - 1 (taps 0, 1, 2 of the kernel's rows), so each x fragment is read
+// from LDS once per kernel column and multiplied with three dy fragments that roll through registers;
+// a chunk stages x rows yy and dy rows yy + 1, and a unit begins with a chunk of dy rows alone. The
+// chunks are double buffered in LDS, with the next chunk's loads in registers during the products (one
+// barrier per chunk); two blocks per CU keep about 50 KB in flight, which is what the path is bound
+// by (0.8 GB of operands per layer at 16 x 512^2).
+// The staged pixels have a pitch (WgradPitch) that puts the 16 pixels of one read on distinct banks.
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// bf16 elements off .. off + 7 (off in 0..2) of the 16 elements held in lo, hi
-__device__ __forceinline__ bf16x8 shifted8(uint4 lo, uint4 hi, int off) {
-    const unsigned d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    union {
-        unsigned u[4];
-        bf16x8 v;
-    } r;
-    if (off == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r.u[j] = d[j];
-    } else if (off == 2) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r.u[j] = d[j + 1];
-    } else {  // one element: each dword takes the high half of one and the low half of the next
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r.u[j] = __builtin_amdgcn_alignbyte(d[j + 1], d[j], 2);
-    }
-    return r.v;
+template <int C>
+struct WgradPitch {  // bf16 per staged pixel: an odd multiple of 32 bytes
+    static constexpr int value = (C % 32 == 0) ? C + 16 : C;
+};
+
+template <int CX, int CY>
+struct WgradCfg {
+    static constexpr int XP = WgradPitch<CX>::value, YP = WgradPitch<CY>::value;
+    static constexpr int RC = 4;                                     // rows per chunk
+    static constexpr int XB = RC * HW * XP, YB = RC * TW * YP;       // bf16 per staged chunk
+    static constexpr size_t LDS = (size_t)2 * (XB + YB) * 2;         // double buffered
+    static constexpr int XU = RC * HW * CX / 8, YU = RC * TW * CY / 8;  // 16-byte units per chunk
+    static constexpr int XN = (XU + THREADS - 1) / THREADS, YN = (YU + THREADS - 1) / THREADS;
+    static constexpr int NCG = CX / 16, MT = CY / 16;
+    static constexpr int WM = 4 / NCG;                // wavefronts that share a group of 16 input channels
+    static constexpr int MTW = (MT + WM - 1) / WM;    // groups of 16 output channels of one wavefront
+};
+
+// the 32 pixels x 16 channels at s (pitch P bf16 per pixel) as one MFMA operand: lane l holds channel
+// l % 16; the order of the pixels is the same for every operand read this way
+template <int P>
+__device__ __forceinline__ bf16x8 tr_frag(const unsigned short* s) {
+    const int l = threadIdx.x % 64;
+    const unsigned short* p = s + (l / 4) * P + (l % 4) * 4;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)p);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 16 * P));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-template <int CINP, int COUTP>
-__global__ __launch_bounds__(THREADS) void k_wgrad(WgradArgs a) {
-    constexpr int MT = COUTP / 16, NTT = 9 * CINP / 16, TT = MT * NTT, TPW = (TT + 3) / 4;
+// units of R rows (a multiple of 4 that divides N); dy has a.dy_ch >= CY channels per pixel
+template <int CX, int CY>
+__global__ __launch_bounds__(THREADS, 2) void k_wgrad(WgradArgs a, int R) {
+    using C = WgradCfg<CX, CY>;
+    constexpr int MTW = C::MTW;
     extern __shared__ unsigned short smem[];
-    unsigned short* s_dy = smem;                      // [COUTP][TH][TW]
-    unsigned short* s_x = smem + COUTP * TH * TW;     // [CINP][HH][XP]
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int lr = l % 16, lk = 8 * (l / 16);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), l = threadIdx.x % 64;
+    // output-channel groups m0, m0 + WM, ...; where that passes the last group (a lone or third one), the
+    // wavefront repeats the last group and does not write it
+    const int cg = w % C::NCG, m0 = C::WM == 1 ? 0 : w / C::NCG;
+    auto group = [&](int j) { return C::MT % C::WM == 0 ? m0 + C::WM * j : min(m0 + C::WM * j, C::MT - 1); };
     const int N = a.N, M = a.M;
-    const int tx = M / TW, ty = N / TH, ntiles = a.batch * tx * ty;
-    f32x4 acc[TPW];
+    const int tx = M / TW, ty = N / R, nunits = a.batch * tx * ty, nc = R / C::RC;
+    // each XCD (blocks b, b + 8, ...) takes a contiguous range of units: neighbouring strips, which
+    // share halo columns, run on one XCD; gridDim.x is a multiple of 8
+    int u, uend;
+    {
+        const int per = (int)gridDim.x / 8, x = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8;
+        const long long lo = ((long long)x * nunits) / 8, hi = ((long long)(x + 1) * nunits) / 8;
+        u = (int)(lo + ((hi - lo) * j) / per);
+        uend = (int)(lo + ((hi - lo) * (j + 1)) / per);
+    }
+    f32x4 acc[9][MTW], accb[MTW];
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float bsum = 0.0f;
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int bx = tile % tx, by = (tile / tx) % ty, b = tile / (tx * ty);
-        const int x0 = bx * TW, y0 = by * TH;
-        __syncthreads();  // the previous tile's LDS reads are done
-        // dy tile, channel-major
-        for (int i = threadIdx.x; i < COUTP * TH * TW; i += THREADS) {
-            const int px = i % TW, r = i / TW, py = r % TH, co = r / TH;
-            s_dy[i] = a.dy[(((size_t)b * N + y0 + py) * M + x0 + px) * a.dy_ch + co];
+    for (int j = 0; j < MTW; ++j) {
+        accb[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    bf16x8 one;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) one[j] = (__bf16)1.0f;
+    // chunk c of unit q: x rows r0 + 4 c .., dy rows r0 + 4 c + 1 .. (the rows wrap around the plane); of chunk
+    // -1 only the dy rows r0 - 1 and r0 are used. Lanes past the last unit load it again, so that no load
+    // is conditional (conditional loads had put the registers into scratch memory).
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 xv[C::XN], yv[C::YN];
+    auto load = [&](int q, int c) {
+        const int x0 = (q % tx) * TW, b = q / (tx * ty), r = ((q / tx) % ty) * R + C::RC * c + N;
+        const u32x4* xs = reinterpret_cast<const u32x4*>(a.xb) + (size_t)b * N * M * (CX / 8);
+        const u32x4* ys = reinterpret_cast<const u32x4*>(a.dy) + (size_t)b * N * M * (a.dy_ch / 8);
+#pragma unroll
+        for (int j = 0; j < C::XN; ++j) {
+            const int i = min((int)threadIdx.x + j * THREADS, C::XU - 1);
+            const int ch = i % (CX / 8), p = i / (CX / 8), px = p % HW, py = p / HW;
+            const int y = (r + py) & (N - 1), x = (x0 + px - 1 + M) & (M - 1);
+            xv[j] = xs[((size_t)y * M + x) * (CX / 8) + ch];
         }
-        // input tile with halo, channel-major
-        for (int i = threadIdx.x; i < CINP * HH * HW; i += THREADS) {
-            const int xx = i % HW, r = i / HW, yy = r % HH, ci = r / HH;
-            const int y = (y0 + yy - 1 + N) & (N - 1), x = (x0 + xx - 1 + M) & (M - 1);
-            s_x[(ci * HH + yy) * XP + xx] = a.xb[(((size_t)b * N + y) * M + x) * CINP + ci];
+#pragma unroll
+        for (int j = 0; j < C::YN; ++j) {
+            const int i = min((int)threadIdx.x + j * THREADS, C::YU - 1);
+            const int ch = i % (CY / 8), p = i / (CY / 8), px = p % TW, py = p / TW;
+            const int y = (r + 1 + py) & (N - 1);
+            yv[j] = ys[((size_t)y * M + x0 + px) * (a.dy_ch / 8) + ch];
         }
+    };
+    auto store = [&](unsigned short* sx, unsigned short* sy) {
+#pragma unroll
+        for (int j = 0; j < C::XN; ++j) {
+            const int i = (int)threadIdx.x + j * THREADS;
+            if (i < C::XU) *reinterpret_cast<u32x4*>(sx + (i / (CX / 8)) * C::XP + (i % (CX / 8)) * 8) = xv[j];
+        }
+#pragma unroll
+        for (int j = 0; j < C::YN; ++j) {
+            const int i = (int)threadIdx.x + j * THREADS;
+            if (i < C::YU) *reinterpret_cast<u32x4*>(sy + (i / (CY / 8)) * C::YP + (i % (CY / 8)) * 8) = yv[j];
+        }
+    };
+    bf16x8 af[3][MTW] = {};  // dy rows yy + 1, yy, yy - 1
+    auto roll = [&](const unsigned short* row) {
+#pragma unroll
+        for (int j = 0; j < MTW; ++j) {
+            af[2][j] = af[1][j];
+            af[1][j] = af[0][j];
+            af[0][j] = tr_frag<C::YP>(row + 16 * group(j));
+        }
+    };
+    int c = -1, buf = 0;
+    if (u < uend) load(u, c);
+    while (u < uend) {
+        unsigned short* sx = smem + buf * (C::XB + C::YB);
+        unsigned short* sy = sx + C::XB;
+        store(sx, sy);
+        const int cc = c;
+        if (++c == nc) {
+            c = -1;
+            ++u;
+        }
+        if (u < uend) load(u, c);
         __syncthreads();
-        if (threadIdx.x < COUTP) {
-            const unsigned short* d = s_dy + threadIdx.x * TH * TW;
-            for (int i = 0; i < TH * TW; ++i) bsum += bf2f(d[i]);
-        }
 #pragma unroll 1
-        for (int r = 0; r < TH; ++r) {
+        for (int r = cc < 0 ? 2 : 0; r < C::RC; ++r) {
+            roll(sy + r * TW * C::YP);
+            if (cc < 0) continue;
 #pragma unroll
-            for (int j = 0; j < TPW; ++j) {
-                const int t = w + 4 * j;
-                if (t < TT) {
-                    const int mt = t % MT, nt = t / MT;
-                    const int tap = nt / (CINP / 16), cg = nt % (CINP / 16);
-                    const int dy = tap / 3, dx = tap % 3;
-                    const bf16x8 afr = *reinterpret_cast<const bf16x8*>(s_dy + ((mt * 16 + lr) * TH + r) * TW + lk);
-                    const uint4* xp =
-                        reinterpret_cast<const uint4*>(s_x + ((cg * 16 + lr) * HH + r + dy) * XP + lk);
-                    const bf16x8 bfr = shifted8(xp[0], xp[1], dx);
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr, bfr, acc[j], 0, 0, 0);
-                }
+            for (int dx = 0; dx < 3; ++dx) {
+                const bf16x8 bf = tr_frag<C::XP>(sx + (r * HW + dx) * C::XP + 16 * cg);
+#pragma unroll
+                for (int j = 0; j < MTW; ++j)
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy)
+                        acc[3 * dy + dx][j] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[dy][j], bf, acc[3 * dy + dx][j], 0, 0, 0);
+            }
+            if (cg == 0) {  // the bias gradient: dy times ones, every dy row once
+#pragma unroll
+                for (int j = 0; j < MTW; ++j)
+                    accb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][j], one, accb[j], 0, 0, 0);
             }
         }
+        buf ^= 1;
     }
     // partial dW in [co][tap][ci] order, then the bias partial
-    float* part = a.part + (size_t)blockIdx.x * (COUTP * 9 * CINP + COUTP);
+    float* part = a.part + (size_t)blockIdx.x * (CY * 9 * CX + CY);
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-        const int t = w + 4 * j;
-        if (t < TT) {
-            const int mt = t % MT, nt = t / MT;
-            const int tap = nt / (CINP / 16), ci = (nt % (CINP / 16)) * 16 + lr;
+    for (int j = 0; j < MTW; ++j) {
+        const int m = m0 + C::WM * j;
+        if (m < C::MT) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int co = mt * 16 + 4 * (l / 16) + i;
-                part[((size_t)co * 9 + tap) * CINP + ci] = acc[j][i];
+                const int co = m * 16 + 4 * (l / 16) + i;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) part[((size_t)co * 9 + t) * CX + cg * 16 + l % 16] = acc[t][j][i];
+                if (cg == 0 && l % 16 == 0) part[CY * 9 * CX + co] = accb[j][i];
             }
         }
     }
-    if (threadIdx.x < COUTP) part[COUTP * 9 * CINP + threadIdx.x] = bsum;
 }
 
-// grads in natural order: dW[co][ci][3][3] (co < cout, ci < cin), then db[co]; sums of nblk partials in order
-__global__ void k_wgrad_reduce(const float* __restrict__ part, float* __restrict__ dW, float* __restrict__ db, int nblk,
-                               int cout, int cin, int coutp, int cinp) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nw = cout * cin * 9;
-    if (i >= nw + cout) return;
-    size_t src;
-    if (i < nw) {
-        const int tap = i % 9, ci = (i / 9) % cin, co = i / (9 * cin);
-        src = ((size_t)co * 9 + tap) * cinp + ci;
-    } else {
-        src = (size_t)coutp * 9 * cinp + (i - nw);
+// grads in natural order: dW[co][ci][3][3] (co < cout, ci < cin), then db[co]; sums of nblk partials in a
+// fixed order. A block sums 32 consecutive values of the partials (128-byte runs), each by 8 threads that
+// take every 8th partial, added in order: 8 us for 512 partials of 18464 values (one thread per value,
+// in the gradients' order, waited for 512 strided loads in turn: 142 us).
+constexpr int RED_V = 32, RED_G = 8;
+__global__ __launch_bounds__(RED_V* RED_G) void k_wgrad_reduce(const float* __restrict__ part, float* __restrict__ dW,
+                                                             float* __restrict__ db, int nblk, int cout, int cin,
+                                                             int coutp, int cinp) {
+    __shared__ float s[RED_G][RED_V];
+    const int v = (int)threadIdx.x % RED_V, g = (int)threadIdx.x / RED_V;
+    const int nw = coutp * 9 * cinp, stride = nw + coutp, src = (int)blockIdx.x * RED_V + v;
+    float t = 0.0f;
+    if (src < stride) {
+#pragma unroll 8
+        for (int b = g; b < nblk; b += RED_G) t += part[(size_t)b * stride + src];
     }
-    const size_t stride = (size_t)coutp * 9 * cinp + coutp;
-    float s = 0.0f;
-    for (int b = 0; b < nblk; ++b) s += part[(size_t)b * stride + src];
-    if (i < nw)
-        dW[i] = s;
-    else
-        db[i - nw] = s;
+    s[g][v] = t;
+    __syncthreads();
+    if (g != 0 || src >= stride) return;
+    t = s[0][v];
+#pragma unroll
+    for (int i = 1; i < RED_G; ++i) t += s[i][v];
+    if (src < nw) {
+        const int ci = src % cinp, tap = (src / cinp) % 9, co = src / (9 * cinp);
+        if (co < cout && ci < cin) dW[((size_t)co * cin + ci) * 9 + tap] = t;
+    } else if (src - nw < cout) {
+        db[src - nw] = t;
+    }
 }
 
 // natural W[co][ci][3][3] -> flipped, transposed bf16 [ci][8 - tap][co], padded to cinp' x coutp'
@@ -1130,15 +1218,20 @@ hipError_t conv_shrink_t(const ConvArgs& a, int batch, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int CINP, int COUTP>
+template <int CX, int CY>
 hipError_t wgrad_t(const WgradArgs& a, int blocks, hipStream_t st) {
-    const void* fn = reinterpret_cast<const void*>(&k_wgrad<CINP, COUTP>);
-    const size_t lds = ((size_t)COUTP * TH * TW + (size_t)CINP * HH * XP) * 2;
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    using C = WgradCfg<CX, CY>;
+    if (blocks % 8 != 0 || a.dy_ch < CY || a.N % 8 != 0 || a.M % TW != 0) return hipErrorInvalidValue;
+    const void* fn = reinterpret_cast<const void*>(&k_wgrad<CX, CY>);
+    if (C::LDS > 65536) {
+        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_wgrad<CINP, COUTP>), dim3((unsigned)blocks), dim3(THREADS), lds, st, a);
+    // rows per unit: as many as leave every block two units (each unit begins with a chunk of dy rows
+    // alone), at least 8
+    int R = 8;
+    while (2 * R <= a.N && (long long)a.batch * (a.M / TW) * (a.N / (2 * R)) >= 2LL * blocks) R *= 2;
+    hipLaunchKernelGGL((k_wgrad<CX, CY>), dim3((unsigned)blocks), dim3(THREADS), C::LDS, st, a, R);
     return hipGetLastError();
 }
 
@@ -1246,9 +1339,9 @@ hipError_t launch_wgrad(int layer, int K, const WgradArgs& a, int blocks, hipStr
 
 hipError_t launch_wgrad_reduce(const float* part, float* dW, float* db, int nblk, int cout, int cin, int coutp, int cinp,
                                hipStream_t st) {
-    const int n = cout * cin * 9 + cout;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, dW, db, nblk, cout, cin,
-                       coutp, cinp);
+    const int n = coutp * 9 * cinp + coutp;
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((n + RED_V - 1) / RED_V)), dim3(RED_V * RED_G), 0, st, part, dW, db,
+                       nblk, cout, cin, coutp, cinp);
     return hipGetLastError();
 }
 
