@@ -313,7 +313,10 @@ int shear_profile_enable(shear_system* s, int on);
 int shear_profile_read(shear_system* s, int* launches, double* total_ms);
 
 /* Column-pass schedule of the separate-launch kernels:
- *   pw_fwd / pw_inv: columns per block (16 or 8; 16 needs cols >= 32);
+ *   pw_fwd / pw_inv: column FFTs per block (16 or 8; 16 needs cols >= 32). In the
+ *     forward they are that many columns; in the inverse, columns times groups
+ *     of filters whose sums the block adds, fewer columns and more groups the
+ *     fewer columns the call has (8 FFTs at 1024 points either way);
  *     pw_fwd = cols / 2 (the whole packed plane per workgroup) selects, for
  *     shear_forward, the whole-plane forward where it is compiled (256 x 256
  *     systems with real filter sets): one workgroup filters a plane,
@@ -325,7 +328,8 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
  *     with the panel form to rounding; kg_fwd and pc_fwd do not apply to it;
  *   kg_fwd / kg_inv: filter groups (1..K: the K filters of a column panel are
  *     split over that many blocks, so that small batches fill the device; the
- *     inverse then adds the groups' partial sums in group order);
+ *     inverse then adds the groups' partial sums in group order). Until it is
+ *     set here or by shear_autotune, kg_fwd follows the batch of each call;
  *   pc_fwd / pc_inv: points per thread of the rows-point column FFTs, i.e.
  *     their radix sequence: the default (8 up to 512 points, 16 at 1024 and
  *     2048) or, at 256 and 512 points, 16 (two radix-16 passes), at 1024
@@ -343,7 +347,8 @@ int shear_set_schedule(shear_system* s, int pw_fwd, int pw_inv, int kg_fwd, int 
 /* Autotuner: chooses the column-pass schedule of each direction among every
  * compiled panel width, filter split in {1, 2, 4, 8} (at most K; the forward
  * also tries 16 and 32 when batch * cols/16 is below the device's compute
- * units) and points per thread (default and alternative, where there is one),
+ * units; the inverse only at 2048 rows, as its blocks split the filters
+ * themselves below that) and points per thread (default and alternative, where there is one),
  * and for the forward also the whole-plane form where it is compiled.
  * Each candidate is timed inside whole shear_forward + shear_inverse steps at
  * this batch size (the forward's candidates with the current inverse schedule,
@@ -351,7 +356,7 @@ int shear_set_schedule(shear_system* s, int pw_fwd, int pw_inv, int kg_fwd, int 
  * coefficients it allocates for the call (batch * (2 + K) * rows * cols
  * floats) and frees before it returns; five interleaved rounds, each
  * candidate keeps the median of its step times. Keeps, for each direction,
- * the candidate with the fewest filter groups among those within 1 % of the
+ * the candidate with the fewest filter groups among those within 0.5 % of the
  * fastest median (shear_set_schedule) and reports it through the out-pointers (any
  * may be NULL); the whole-plane forward is taken where its median is below the
  * chosen panel schedule's (pw_fwd then reports cols / 2, and the panel

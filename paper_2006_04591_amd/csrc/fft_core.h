@@ -267,13 +267,23 @@ __device__ __forceinline__ void fft(float2 (&v)[P], float2* s, int t, const floa
     FFTPass<L, P, INV, 1, true>::run(v, s, t, tw);
 }
 
+// A value of a filter set (float or float2) and its product with a spectrum value.
+template <bool REAL>
+struct FVal {
+    typedef float type;
+    static __device__ __forceinline__ float load(const void* f, size_t i) { return reinterpret_cast<const float*>(f)[i]; }
+    static __device__ __forceinline__ float2 mul(float2 a, float f) { return cscale(a, f); }
+};
+template <>
+struct FVal<false> {
+    typedef float2 type;
+    static __device__ __forceinline__ float2 load(const void* f, size_t i) { return reinterpret_cast<const float2*>(f)[i]; }
+    static __device__ __forceinline__ float2 mul(float2 a, float2 f) { return cmul(a, f); }
+};
+
 template <bool REAL>
 __device__ __forceinline__ float2 fmul(const void* __restrict__ f, size_t i, float2 a) {
-    if constexpr (REAL) {
-        return cscale(a, reinterpret_cast<const float*>(f)[i]);
-    } else {
-        return cmul(a, reinterpret_cast<const float2*>(f)[i]);
-    }
+    return FVal<REAL>::mul(a, FVal<REAL>::load(f, i));
 }
 
 }  // namespace dev

@@ -15,10 +15,11 @@ struct DevPlan {
     const float2* twN = nullptr;  // exp(-2 pi i m / N), m < N
     const float2* twL = nullptr;  // exp(-2 pi i m / L), m < L
     const float2* twM = nullptr;  // exp(-2 pi i m / M), m < M
-    int pw_fwd = 16;          // columns per block of the column passes (16 or 8; 8 when L < 16)
-    int pw_inv = 16;
-    int kg_fwd = 1;           // filter groups of the column passes (blocks per panel; capped at K)
-    int kg_inv = 1;
+    int cus = 1;              // compute units of the device
+    int pw_fwd = 8;           // columns per block of the forward column pass (16 or 8; 8 when L < 16)
+    int pw_inv = 16;          // column FFTs per block of the inverse (16 or 8): columns x groups of filters
+    int kg_fwd = 0;           // filter groups of the forward (blocks per panel; capped at K), 0: by batch
+    int kg_inv = 1;           // filter groups over blocks of the inverse (partial sums in memory)
     int pc_fwd = 0;           // points per thread of the column FFTs (0: col_points_default(N); else
     int pc_inv = 0;           // col_points_alternative(N), a different radix sequence)
     bool plane_fwd = false;   // shear_forward uses launch_plane_fwd (where plane_fwd_supported)
@@ -66,9 +67,10 @@ hipError_t launch_cols_fwd(const DevPlan& d, const float2* A, float2* T, int nim
                            hipStream_t st);
 
 // Inverse / adjoint, column stage, K-reducing: V[b] = colIFFT( sum_k filt_k (.) colFFT(U[b][k]) ).
-// part: cols_inv_part_elems(d, nimg) float2 of scratch (may be null when that is 0).
-hipError_t launch_cols_inv(const DevPlan& d, const float2* U, float2* V, int nimg, const void* filt, float2* part,
-                           hipStream_t st);
+// part: cols_inv_part_elems(d, nimg) float2 of scratch (may be null when that is 0). batch: the images of
+// the whole call, of which these nimg are a chunk (the split of a block's FFTs follows it).
+hipError_t launch_cols_inv(const DevPlan& d, const float2* U, float2* V, int nimg, int batch, const void* filt,
+                           float2* part, hipStream_t st);
 
 // Whole-plane forward (one workgroup per (image, filter) plane, its transposition on chip),
 // available for 256 x 256 systems with real filter sets. Its operands are residue-major: element

@@ -268,55 +268,53 @@ __device__ __forceinline__ void col_fwd_emit(const float2 (&xh)[P], const void* 
     for (int q = 0; q < P; ++q) st_x<XS>(out_plane + xoff(t + T * q, col, N), y[q]);
 }
 
-// The mirrored-term accumulator g of packed column 0 lives in the panel's
-// mirror buffer (N float2 of LDS after the FFT scratches), written only by the
-// threads of column 0, each on its own entries: it costs no registers.
-template <int N, int P, int PW>
-__device__ __forceinline__ void col_inv_begin(int col0, float2* lds, const int tid) {
+// The mirrored-term accumulator g of packed column 0 lives in a mirror buffer smir (N float2 of LDS),
+// written only by the threads of column 0, each on its own entries: it costs no registers.
+template <int N, int P>
+__device__ __forceinline__ void col_inv_begin(int col, int t, float2* smir) {
     constexpr int T = N / P;
-    const int t = tid % T, c = tid / T;
-    float2* smir = lds + PW * ColScratch<N, P>::value;
-    if (col0 + c == 0) {
+    if (col == 0) {
 #pragma unroll
         for (int q = 0; q < P; ++q) smir[t + T * q] = make_float2(0.0f, 0.0f);
     }
 }
 
-// acc += filter_k (.) colFFT(u panel); packed column 0 also accumulates g for the mirrored term.
-template <int N, int P, int PW, bool REAL, bool XS = true>
+// acc += filter_k (.) colFFT(column col of u); packed column 0 also accumulates g for the mirrored term.
+template <int N, int P, bool REAL, bool XS = true>
 __device__ __forceinline__ void col_inv_accum(const float2* __restrict__ u_plane, const void* __restrict__ filt, int k,
-                                              int L, int col0, float2 (&acc)[P], float2* lds,
-                                              const float2* __restrict__ twN, const int tid) {
+                                              int L, int col, int t, float2 (&acc)[P], float2* s,
+                                              float2* smir,
+                                              const float2* __restrict__ twN) {
     constexpr int T = N / P;
-    const int t = tid % T, c = tid / T;
-    const int col = col0 + c;
-    float2* s = lds + c * ColScratch<N, P>::value;
     float2 x[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) x[q] = ld_x<XS>(u_plane + xoff(t + T * q, col, N));
     fft<N, P, false>(x, s, t, twN);
     const size_t fstride = (size_t)(L + 1) * N;
     const size_t fbase = (size_t)k * fstride + (size_t)col * N;
+    typename FVal<REAL>::type f[P];
 #pragma unroll
-    for (int q = 0; q < P; ++q) acc[q] = cadd(acc[q], fmul<REAL>(filt, fbase + t + T * q, x[q]));
+    for (int q = 0; q < P; ++q) f[q] = FVal<REAL>::load(filt, fbase + t + T * q);
     if (col == 0) {
-        float2* g = lds + PW * ColScratch<N, P>::value;
+        // every load is issued before the first LDS store (a load between the stores waits for the one
+        // before it, and column 0's wavefront, alone in the extra work, is the last to finish)
+        typename FVal<REAL>::type h[P];
         const size_t gbase = (size_t)k * fstride + (size_t)L * N;
 #pragma unroll
-        for (int q = 0; q < P; ++q) g[t + T * q] = cadd(g[t + T * q], fmul<REAL>(filt, gbase + t + T * q, x[q]));
+        for (int q = 0; q < P; ++q) h[q] = FVal<REAL>::load(filt, gbase + t + T * q);
+#pragma unroll
+        for (int q = 0; q < P; ++q) smir[t + T * q] = cadd(smir[t + T * q], FVal<REAL>::mul(x[q], h[q]));
     }
+#pragma unroll
+    for (int q = 0; q < P; ++q) acc[q] = cadd(acc[q], FVal<REAL>::mul(x[q], f[q]));
 }
 
-// v panel = colIFFT(acc + [column 0: conj g(-m)]), g in the mirror buffer
-template <int N, int P, int PW>
-__device__ __forceinline__ void col_inv_finish(float2 (&acc)[P], int col0, float2* __restrict__ v_img, float2* lds,
-                                               const float2* __restrict__ twN, const int tid) {
+// column col of v = colIFFT(acc + [column 0: conj g(-m)]), g in the mirror buffer, every entry of which
+// has been written before the caller's last barrier
+template <int N, int P>
+__device__ __forceinline__ void col_inv_finish(float2 (&acc)[P], int col, int t, float2* __restrict__ v_img, float2* s,
+                                               const float2* smir, const float2* __restrict__ twN) {
     constexpr int T = N / P;
-    const int t = tid % T, c = tid / T;
-    const int col = col0 + c;
-    float2* s = lds + c * ColScratch<N, P>::value;
-    const float2* smir = lds + PW * ColScratch<N, P>::value;
-    __syncthreads();  // every thread of column 0 has finished its entries of g
     if (col == 0) {
 #pragma unroll
         for (int q = 0; q < P; ++q) {
@@ -536,41 +534,78 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_fwd(const
                                      (int)threadIdx.x);
 }
 
+// A block takes PW columns; its G thread groups (PW N/P threads each) take every G-th filter of the
+// block's range k0 + i, and their sums are added in LDS in group order. G > 1 lets a block take fewer
+// columns with as many threads, so that a small batch's columns alone give every compute unit a block
+// and its K filters pass in K/G steps (inv_width chooses).
+template <int N, int PW, int PP, int G>
+struct ColInvCfg {
+    static constexpr int P = PP;
+    static constexpr int T = N / P;
+    static constexpr int THREADS = PW * T * G;
+    static constexpr size_t LDS = (size_t)G * (PW * ColScratch<N, P>::value + N) * sizeof(float2);
+    static_assert(G == 1 || T <= 64, "groups of filters need FFTs within a wavefront (no barriers in their loops)");
+};
+
 // kg == 1: V[b] = colIFFT(sum_k ...); kg > 1: part[b][g] (L x N column-major) and, for packed
 // column 0, part0[b][g] (N) receive the group's sums.
-template <int N, int PW, bool REAL, int PP>
-__global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_inv(const float2* __restrict__ U,
-                                                                    float2* __restrict__ V,
-                                                                    const void* __restrict__ filt, int L, int K,
-                                                                    int npan, int kper, int kg,
-                                                                    float2* __restrict__ part,
-                                                                    float2* __restrict__ part0,
-                                                                    const float2* __restrict__ twN) {
-    constexpr int P = ColCfg<N, PW, PP>::P, T = N / P;
+template <int N, int PW, bool REAL, int PP, int G>
+__global__ __launch_bounds__((ColInvCfg<N, PW, PP, G>::THREADS)) void k_cols_inv(const float2* __restrict__ U,
+                                                                        float2* __restrict__ V,
+                                                                        const void* __restrict__ filt, int L, int K,
+                                                                        int npan, int kper, int kg,
+                                                                        float2* __restrict__ part,
+                                                                        float2* __restrict__ part0,
+                                                                        const float2* __restrict__ twN) {
+    constexpr int P = PP, T = N / P, CS = ColScratch<N, P>::value;
     extern __shared__ float2 lds[];
     const int pan = blockIdx.x % npan, g = (blockIdx.x / npan) % kg, b = blockIdx.x / (npan * kg);
-    const int tid = (int)threadIdx.x;
+    const int tid = (int)threadIdx.x, t = tid % T, fg = tid / T, c = G == 1 ? fg : fg % PW,
+              kk = G == 1 ? 0 : fg / PW, col = pan * PW + c;
+    float2* smir = lds + kk * N;
+    float2* s = lds + G * N + fg * CS;
     float2 acc[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) acc[q] = make_float2(0.0f, 0.0f);
-    col_inv_begin<N, P, PW>(pan * PW, lds, tid);
+    col_inv_begin<N, P>(col, t, smir);
     const int k1 = min(K, (g + 1) * kper);
-    for (int k = g * kper; k < k1; ++k)
-        col_inv_accum<N, P, PW, REAL>(U + ((size_t)b * K + k) * L * N, filt, k, L, pan * PW, acc, lds, twN, tid);
+    for (int k = g * kper + kk; k < k1; k += G)
+        col_inv_accum<N, P, REAL>(U + ((size_t)b * K + k) * L * N, filt, k, L, col, t, acc, s, smir, twN);
+    if constexpr (G > 1) {
+        // (a group's last FFT has read its scratch: the wavefront's LDS operations execute in order)
+        wave_sync();
+        if (kk > 0) {
+#pragma unroll
+            for (int q = 0; q < P; ++q) s[t + T * q] = acc[q];
+        }
+        __syncthreads();
+        if (kk == 0) {
+#pragma unroll
+            for (int i = 1; i < G; ++i)
+#pragma unroll
+                for (int q = 0; q < P; ++q) acc[q] = cadd(acc[q], s[i * PW * CS + t + T * q]);
+            if (col == 0) {
+#pragma unroll
+                for (int i = 1; i < G; ++i)
+#pragma unroll
+                    for (int q = 0; q < P; ++q) smir[t + T * q] = cadd(smir[t + T * q], smir[i * N + t + T * q]);
+            }
+        }
+    }
     if (kg == 1) {
-        col_inv_finish<N, P, PW>(acc, pan * PW, V + (size_t)b * L * N, lds, twN, tid);
+        __syncthreads();  // every thread of column 0 has finished its entries of g
+        if (kk == 0) col_inv_finish<N, P>(acc, col, t, V + (size_t)b * L * N, s, smir, twN);
         return;
     }
-    const int t = tid % T, c = tid / T, col = pan * PW + c;
+    if (kk != 0) return;
     float2* o = part + ((size_t)b * kg + g) * L * N + (size_t)col * N;
 #pragma unroll
     for (int q = 0; q < P; ++q) o[t + T * q] = acc[q];
     if (col == 0) {
         // each thread of column 0 reads back the entries of the mirrored-term sum it accumulated
-        const float2* sg = lds + PW * ColScratch<N, P>::value;
         float2* og = part0 + ((size_t)b * kg + g) * N;
 #pragma unroll
-        for (int q = 0; q < P; ++q) og[t + T * q] = sg[t + T * q];
+        for (int q = 0; q < P; ++q) og[t + T * q] = smir[t + T * q];
     }
 }
 
@@ -580,11 +615,12 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_inv_finis
                                                                            const float2* __restrict__ part0,
                                                                            float2* __restrict__ V, int L, int npan,
                                                                            int kg, const float2* __restrict__ twN) {
-    constexpr int P = ColCfg<N, PW, PP>::P, T = N / P;
+    constexpr int P = ColCfg<N, PW, PP>::P, T = N / P, CS = ColScratch<N, P>::value;
     extern __shared__ float2 lds[];
     const int pan = blockIdx.x % npan, b = blockIdx.x / npan;
     const int tid = (int)threadIdx.x;
     const int t = tid % T, c = tid / T, col = pan * PW + c;
+    float2* smir = lds + PW * CS;
     float2 acc[P], gg[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) acc[q] = gg[q] = make_float2(0.0f, 0.0f);
@@ -599,11 +635,11 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_inv_finis
         }
     }
     if (col == 0) {
-        float2* smir = lds + PW * ColScratch<N, P>::value;
 #pragma unroll
         for (int q = 0; q < P; ++q) smir[t + T * q] = gg[q];
     }
-    col_inv_finish<N, P, PW>(acc, pan * PW, V + (size_t)b * L * N, lds, twN, tid);
+    __syncthreads();  // every thread of column 0 has written its entries of the mirror buffer
+    col_inv_finish<N, P>(acc, col, t, V + (size_t)b * L * N, lds + c * CS, smir, twN);
 }
 
 __global__ void k_zero_u32(unsigned* p, int n) {
@@ -928,13 +964,24 @@ inline void kgroups(int K, int kg_req, int& kper, int& kg) {
     kg = (K + kper - 1) / kper;
 }
 
+// Filter groups of the forward column pass where the plan leaves them open (kg_fwd 0): as many as give
+// the device 512 threads per compute unit. A group costs the panel's column FFT again, so a batch
+// whose panels alone do that is not split. Measured in 8-column panels (us; groups): one 512 x 512 image
+// of 49 filters 1: 85, 8: 17.0, 16: 18.3, 49: 33.5, four 2: 45.7, 8: 49.3; 256 x 256 x 33 one image 1: 39,
+// 33: 8.8, eight 4: 17.2, 8: 20.9, thirty-two 1: 57.5, 8: 63.1; three 1024 x 1024 x 49 1: 127, 4: 147.
+inline int fwd_groups(const DevPlan& d, int panels, int threads) {
+    if (d.kg_fwd > 0) return d.kg_fwd;
+    const long long have = (long long)panels * threads, want = 512LL * d.cus;
+    return (int)std::min<long long>(d.K, std::max<long long>(1, (want + have / 2) / have));
+}
+
 template <int N, int PW, int PP>
 hipError_t cols_fwd_t(const DevPlan& d, const float2* A, float2* T, int nimg, const void* filt, float scale,
                       hipStream_t st) {
     using C = ColCfg<N, PW, PP>;
     const int npan = d.L / PW;
     int kper, kg;
-    kgroups(d.K, d.kg_fwd, kper, kg);
+    kgroups(d.K, fwd_groups(d, npan * nimg, C::THREADS), kper, kg);
     const size_t blocks = (size_t)npan * kg * nimg;
     if (d.real) {
         hipError_t e = set_lds(k_cols_fwd<N, PW, true, PP>, C::LDS);
@@ -950,10 +997,10 @@ hipError_t cols_fwd_t(const DevPlan& d, const float2* A, float2* T, int nimg, co
     return hipGetLastError();
 }
 
-template <int N, int PW, int PP>
+template <int N, int PW, int PP, int G>
 hipError_t cols_inv_t(const DevPlan& d, const float2* U, float2* V, int nimg, const void* filt, float2* part,
                       hipStream_t st) {
-    using C = ColCfg<N, PW, PP>;
+    using C = ColInvCfg<N, PW, PP, G>;
     const int npan = d.L / PW;
     int kper, kg;
     kgroups(d.K, d.kg_inv, kper, kg);
@@ -961,23 +1008,26 @@ hipError_t cols_inv_t(const DevPlan& d, const float2* U, float2* V, int nimg, co
     float2* part0 = kg > 1 ? part + (size_t)nimg * kg * d.L * d.N : nullptr;
     const size_t blocks = (size_t)npan * kg * nimg;
     if (d.real) {
-        hipError_t e = set_lds(k_cols_inv<N, PW, true, PP>, C::LDS);
+        hipError_t e = set_lds(k_cols_inv<N, PW, true, PP, G>, C::LDS);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_cols_inv<N, PW, true, PP>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, U, V,
+        hipLaunchKernelGGL((k_cols_inv<N, PW, true, PP, G>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, U, V,
                            filt, d.L, d.K, npan, kper, kg, part, part0, d.twN);
     } else {
-        hipError_t e = set_lds(k_cols_inv<N, PW, false, PP>, C::LDS);
+        hipError_t e = set_lds(k_cols_inv<N, PW, false, PP, G>, C::LDS);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_cols_inv<N, PW, false, PP>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, U, V,
+        hipLaunchKernelGGL((k_cols_inv<N, PW, false, PP, G>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, U, V,
                            filt, d.L, d.K, npan, kper, kg, part, part0, d.twN);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || kg == 1) return e;
-    e = set_lds(k_cols_inv_finish<N, PW, PP>, C::LDS);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_cols_inv_finish<N, PW, PP>), dim3((unsigned)((size_t)npan * nimg)), dim3(C::THREADS), C::LDS, st,
-                       part, part0, V, d.L, npan, kg, d.twN);
-    return hipGetLastError();
+    if constexpr (G == 1) {
+        e = set_lds(k_cols_inv_finish<N, PW, PP>, C::LDS);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_cols_inv_finish<N, PW, PP>), dim3((unsigned)((size_t)npan * nimg)), dim3(C::THREADS), C::LDS,
+                           st, part, part0, V, d.L, npan, kg, d.twN);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;  // groups within a block and across blocks do not mix
 }
 
 // The alternative points per thread of an N-point column FFT (a different radix sequence), 0 where
@@ -1000,14 +1050,78 @@ hipError_t cols_fwd_pc(const DevPlan& d, const float2* A, float2* T, int nimg, c
     return cols_fwd_t<N, PW, ColPts<N>::value>(d, A, T, nimg, filt, scale, st);
 }
 
-template <int N, int PW>
-hipError_t cols_inv_pc(const DevPlan& d, const float2* U, float2* V, int nimg, const void* filt, float2* part,
-                       hipStream_t st) {
-    constexpr int ALT = alt_col_pts<N>();
-    if constexpr (ALT > 0 && PW * (N / ALT) <= 1024) {
-        if (d.pc_inv == ALT) return cols_inv_t<N, PW, ALT>(d, U, V, nimg, filt, part, st);
+// Columns per block of the inverse column pass, for blocks of S FFTs (S / PW groups of filters): the most
+// that still give the device 768 threads per compute unit (1024 points: 512, and 1024 above 2 columns).
+// Measured inside forward + inverse steps (us, columns x groups):
+//   512 x 512 x 49, 1 image   1 x 16: 19.5   2 x 8: 23.7   4 x 4: 36.8   8 x 2: 60.3   16 x 1: 113
+//                   4 images  1 x 16: 66.0   2 x 8: 50.7   4 x 4: 44.5   8 x 2: 64.6   16 x 1: 116
+//                  16 images  1 x 16: 252    2 x 8: 195    4 x 4: 171    8 x 2: 157    16 x 1: 143
+//   256 x 256 x 33, 8 images  1 x 16: 26.3   2 x 8: 19.7   4 x 4: 22.3   8 x 2: 34.1   16 x 1: 71.2
+//                  32 images  1 x 16: 91.6   2 x 8: 69.9   4 x 4: 60.6   8 x 2: 53.3   16 x 1: 79.8
+//   1024 x 1024 x 49, 1 image  1 x 8: 59.8   2 x 4: 53.1   4 x 2: 78.8   8 x 1: 138
+//                    3 images  1 x 8: 167    2 x 4: 145    4 x 2: 156    8 x 1: 148
+//                    6 images  1 x 8: 326    2 x 4: 282    4 x 2: 251    8 x 1: 291
+// Splitting the filters over blocks with partial sums in memory (kg_inv 2 to 8) was slower throughout
+// (28.3 at best for one 512 x 512 image, 28.0 and 66.4 for 8 and 32 of 256 x 256). Not below 2 columns
+// where an FFT is less than half a wavefront (128 x 128 x 17, 4 images: 2 x 8 9.1, 1 x 16 9.9).
+// The rule takes the call's whole batch, not a chunk of it, so that chunks sum in the same order.
+template <int N, int T, int S>
+int inv_width(const DevPlan& d, int batch) {
+    constexpr int lo = T >= 32 ? 1 : 2, hi = N >= 1024 ? 4 : S;
+    int pw = std::min(hi, d.L);
+    auto want = [&] { return (N >= 1024 ? (pw > 2 ? 1024LL : 512LL) : 768LL) * d.cus; };
+    while (pw > lo && (long long)batch * (d.L / pw) * (S * T) < want()) pw /= 2;
+    return pw;
+}
+
+template <int N, int PP, int S>
+hipError_t cols_inv_s(const DevPlan& d, const float2* U, float2* V, int nimg, int batch, const void* filt, float2* part,
+                      hipStream_t st) {
+    constexpr int T = N / PP;
+    if constexpr (T <= 64) {
+        if (d.kg_inv > 1) return cols_inv_t<N, 8, PP, 1>(d, U, V, nimg, filt, part, st);
+        switch (inv_width<N, T, S>(d, batch)) {
+            case 1:
+                if constexpr (T >= 32) return cols_inv_t<N, 1, PP, S>(d, U, V, nimg, filt, part, st);
+                break;
+            case 2: return cols_inv_t<N, 2, PP, S / 2>(d, U, V, nimg, filt, part, st);
+            case 4: return cols_inv_t<N, 4, PP, S / 4>(d, U, V, nimg, filt, part, st);
+            case 8:
+                if constexpr (N < 1024) return cols_inv_t<N, 8, PP, S / 8>(d, U, V, nimg, filt, part, st);
+                break;
+            case 16:
+                if constexpr (N < 1024 && S == 16) return cols_inv_t<N, 16, PP, 1>(d, U, V, nimg, filt, part, st);
+                break;
+        }
+        return hipErrorInvalidValue;
+    } else {
+        return cols_inv_t<N, (N >= 2048 ? 4 : 8), PP, 1>(d, U, V, nimg, filt, part, st);
     }
-    return cols_inv_t<N, PW, ColPts<N>::value>(d, U, V, nimg, filt, part, st);
+}
+
+// The inverse column pass at the plan's FFTs per block (pw_inv) and points per thread. 1024 points: 16
+// FFTs per block do not fit in registers (a 1024-thread block may hold 128 a lane: 236 bytes of
+// scratch, 718 us for three images of 49 filters against 145), so the width asked for only decides
+// whether the alternative points per thread apply, as it did.
+template <int N>
+hipError_t cols_inv_n(const DevPlan& d, const float2* U, float2* V, int nimg, int batch, const void* filt, float2* part,
+                      hipStream_t st) {
+    constexpr int ALT = alt_col_pts<N>(), DEF = ColPts<N>::value;
+    const bool wide = d.L >= 16 && d.pw_inv == 16;
+    if constexpr (N <= 512) {
+        if constexpr (ALT > 0) {
+            if (d.pc_inv == ALT)
+                return wide ? cols_inv_s<N, ALT, 16>(d, U, V, nimg, batch, filt, part, st)
+                            : cols_inv_s<N, ALT, 8>(d, U, V, nimg, batch, filt, part, st);
+        }
+        return wide ? cols_inv_s<N, DEF, 16>(d, U, V, nimg, batch, filt, part, st)
+                    : cols_inv_s<N, DEF, 8>(d, U, V, nimg, batch, filt, part, st);
+    } else {
+        if constexpr (ALT > 0) {
+            if (d.pc_inv == ALT && !wide) return cols_inv_s<N, ALT, 8>(d, U, V, nimg, batch, filt, part, st);
+        }
+        return cols_inv_s<N, DEF, 8>(d, U, V, nimg, batch, filt, part, st);
+    }
 }
 
 // whole-plane forward: column spectra of the images (residue-major), then one workgroup per plane
@@ -1132,43 +1246,54 @@ hipError_t launch_rows_thresh(const DevPlan& d, float2* planes, int nplanes, con
     return hipErrorInvalidValue;
 }
 
-// PW8_1024: the block width that serves 8-column panels at N = 1024 (4 for the forward pass:
-// two 256-thread blocks per CU instead of one of 512 at the same register-bound occupancy,
-// 0.22 -> 0.20 ms in the uneven inpainting; the inverse stays at 8, which measured faster there)
-#define SHEAR_COLS_SWITCH(PWSEL, PW8_1024, FN, ...)                                \
-    if (d.L >= 16 && (PWSEL) == 16) {                                              \
-        switch (d.N) {                                                             \
-            case 16: return FN<16, 16>(__VA_ARGS__);                               \
-            case 32: return FN<32, 16>(__VA_ARGS__);                               \
-            case 64: return FN<64, 16>(__VA_ARGS__);                               \
-            case 128: return FN<128, 16>(__VA_ARGS__);                             \
-            case 256: return FN<256, 16>(__VA_ARGS__);                             \
-            case 512: return FN<512, 16>(__VA_ARGS__);                             \
-            case 1024: return FN<1024, 16>(__VA_ARGS__);                           \
-            case 2048: return FN<2048, 4>(__VA_ARGS__);                            \
-        }                                                                          \
-    } else if (d.L >= 8) {                                                         \
-        switch (d.N) {                                                             \
-            case 16: return FN<16, 8>(__VA_ARGS__);                                \
-            case 32: return FN<32, 8>(__VA_ARGS__);                                \
-            case 64: return FN<64, 8>(__VA_ARGS__);                                \
-            case 128: return FN<128, 8>(__VA_ARGS__);                              \
-            case 256: return FN<256, 8>(__VA_ARGS__);                              \
-            case 512: return FN<512, 8>(__VA_ARGS__);                              \
-            case 1024: return FN<1024, PW8_1024>(__VA_ARGS__);                     \
-            case 2048: return FN<2048, 4>(__VA_ARGS__);                            \
-        }                                                                          \
-    }                                                                              \
-    return hipErrorInvalidValue;
-
+// Column passes in panels of the plan's width. 1024 points: 4-column blocks (two 256-thread blocks per CU
+// instead of one of 512 at the same register-bound occupancy, 0.22 -> 0.20 ms in the uneven inpainting;
+// 16-column blocks spill 196 bytes a lane, 373 us for three images of 49 filters against 127), the
+// alternative points per thread only where 8-column panels are asked for. 2048 points: 4 columns.
 hipError_t launch_cols_fwd(const DevPlan& d, const float2* A, float2* T, int nimg, const void* filt, float scale,
                            hipStream_t st) {
-    SHEAR_COLS_SWITCH(d.pw_fwd, 4, cols_fwd_pc, d, A, T, nimg, filt, scale, st)
+    const bool wide = d.L >= 16 && d.pw_fwd == 16;
+    if (d.L < 8) return hipErrorInvalidValue;
+    if (wide) {
+        switch (d.N) {
+            case 16: return cols_fwd_pc<16, 16>(d, A, T, nimg, filt, scale, st);
+            case 32: return cols_fwd_pc<32, 16>(d, A, T, nimg, filt, scale, st);
+            case 64: return cols_fwd_pc<64, 16>(d, A, T, nimg, filt, scale, st);
+            case 128: return cols_fwd_pc<128, 16>(d, A, T, nimg, filt, scale, st);
+            case 256: return cols_fwd_pc<256, 16>(d, A, T, nimg, filt, scale, st);
+            case 512: return cols_fwd_pc<512, 16>(d, A, T, nimg, filt, scale, st);
+            case 1024: return cols_fwd_t<1024, 4, ColPts<1024>::value>(d, A, T, nimg, filt, scale, st);
+            case 2048: return cols_fwd_pc<2048, 4>(d, A, T, nimg, filt, scale, st);
+        }
+    } else {
+        switch (d.N) {
+            case 16: return cols_fwd_pc<16, 8>(d, A, T, nimg, filt, scale, st);
+            case 32: return cols_fwd_pc<32, 8>(d, A, T, nimg, filt, scale, st);
+            case 64: return cols_fwd_pc<64, 8>(d, A, T, nimg, filt, scale, st);
+            case 128: return cols_fwd_pc<128, 8>(d, A, T, nimg, filt, scale, st);
+            case 256: return cols_fwd_pc<256, 8>(d, A, T, nimg, filt, scale, st);
+            case 512: return cols_fwd_pc<512, 8>(d, A, T, nimg, filt, scale, st);
+            case 1024: return cols_fwd_pc<1024, 4>(d, A, T, nimg, filt, scale, st);
+            case 2048: return cols_fwd_pc<2048, 4>(d, A, T, nimg, filt, scale, st);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_cols_inv(const DevPlan& d, const float2* U, float2* V, int nimg, const void* filt, float2* part,
-                           hipStream_t st) {
-    SHEAR_COLS_SWITCH(d.pw_inv, 8, cols_inv_pc, d, U, V, nimg, filt, part, st)
+hipError_t launch_cols_inv(const DevPlan& d, const float2* U, float2* V, int nimg, int batch, const void* filt,
+                           float2* part, hipStream_t st) {
+    if (d.L < 8) return hipErrorInvalidValue;
+    switch (d.N) {
+        case 16: return cols_inv_n<16>(d, U, V, nimg, batch, filt, part, st);
+        case 32: return cols_inv_n<32>(d, U, V, nimg, batch, filt, part, st);
+        case 64: return cols_inv_n<64>(d, U, V, nimg, batch, filt, part, st);
+        case 128: return cols_inv_n<128>(d, U, V, nimg, batch, filt, part, st);
+        case 256: return cols_inv_n<256>(d, U, V, nimg, batch, filt, part, st);
+        case 512: return cols_inv_n<512>(d, U, V, nimg, batch, filt, part, st);
+        case 1024: return cols_inv_n<1024>(d, U, V, nimg, batch, filt, part, st);
+        case 2048: return cols_inv_n<2048>(d, U, V, nimg, batch, filt, part, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 bool plane_fwd_supported(const DevPlan& d) { return d.real && d.N == 256 && d.M == 256; }

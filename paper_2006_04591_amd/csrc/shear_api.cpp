@@ -234,6 +234,7 @@ int finish_system(shear_system* s, std::string& why) {
         why = std::string("querying the compute-unit count failed: ") + hipGetErrorString(e);
         return SHEAR_E_HIP;
     }
+    s->plan.cus = std::max(1, s->cus);
     return SHEAR_OK;
 }
 
@@ -387,7 +388,7 @@ int inverse_like(shear_system* s, const float* coeffs, float* x, int batch, void
         });
         if (e != hipSuccess) return hip_fail(e, "row r2c launch");
         e = timed(s, SHEAR_KERNEL_COLS_INV, st, [&] {
-            return shear::launch_cols_inv(d, U, V + (size_t)b0 * pb, nb, filt, part_ptr(s, batch, chunk), st);
+            return shear::launch_cols_inv(d, U, V + (size_t)b0 * pb, nb, batch, filt, part_ptr(s, batch, chunk), st);
         });
         if (e != hipSuccess) return hip_fail(e, "column pass launch");
     }
@@ -742,7 +743,7 @@ int shear_denoise(shear_system* s, const float* x, float* y, int batch, const fl
         if (e != hipSuccess) return hip_fail(e, "row threshold launch");
         // the images of this chunk no longer need their row spectra: the sums replace them
         e = timed(s, SHEAR_KERNEL_COLS_INV, st, [&] {
-            return shear::launch_cols_inv(d, T, A + (size_t)b0 * pb, nb, s->filt_inv, part_ptr(s, batch, chunk), st);
+            return shear::launch_cols_inv(d, T, A + (size_t)b0 * pb, nb, batch, s->filt_inv, part_ptr(s, batch, chunk), st);
         });
         if (e != hipSuccess) return hip_fail(e, "column pass launch");
     }
@@ -780,7 +781,7 @@ hipError_t enqueue_inpaint(shear_system* s, const float* fm, const float* mask, 
             });
             if (e != hipSuccess) return e;
             e = timed(s, SHEAR_KERNEL_COLS_INV, st, [&] {
-                return shear::launch_cols_inv(d, T, A + (size_t)b0 * pb, nb, s->filt_inv, part_ptr(s, batch, chunk), st);
+                return shear::launch_cols_inv(d, T, A + (size_t)b0 * pb, nb, batch, s->filt_inv, part_ptr(s, batch, chunk), st);
             });
             if (e != hipSuccess) return e;
         }
@@ -991,13 +992,16 @@ int shear_autotune(shear_system* s, int batch, int* pw_fwd, int* pw_inv, int* kg
     // there is one
     std::vector<int> pcs = {shear::col_points_default(s->rows)};
     if (shear::col_points_alternative(s->rows)) pcs.push_back(shear::col_points_alternative(s->rows));
-    // filter splits: up to 8 groups in the inverse (each group adds a partial-sum plane per image);
-    // the forward, which needs no partial sums, also tries 16 and 32 when the batch's panels alone
-    // (at 8 columns) would leave the device's compute units idle
+    // filter splits over blocks: the forward, which needs no partial sums, tries up to 8 groups, and 16
+    // and 32 when the batch's panels alone (at 8 columns) would leave the device's compute units idle. The
+    // inverse splits the filters within its blocks by itself (launch_cols_inv), which was faster than
+    // partial sums at every size and batch measured; only 2048-point columns, whose blocks cannot, try up
+    // to 8 groups (each adds a partial-sum plane per image).
     std::vector<int> kgs, kgs_fwd;
     for (int kg : {1, 2, 4, 8})
         if (kg <= s->K) kgs.push_back(kg);
     kgs_fwd = kgs;
+    if (s->rows < 2048) kgs = {1};
     if ((long long)batch * (s->cols / 2 / 8) < (long long)s->cus)
         for (int kg : {16, 32})
             if (kg <= s->K) kgs_fwd.push_back(kg);
@@ -1089,11 +1093,13 @@ int shear_autotune(shear_system* s, int batch, int* pw_fwd, int* pw_inv, int* kg
         }
         // a filter split adds work (the forward repeats a panel's column FFT per group, the inverse
         // writes and adds partial sums), so it is taken only where it is measurably faster: among
-        // the candidates within 1 % of the fastest step, the fewest groups, then the fastest
+        // the candidates within 0.5 % of the fastest step (the medians of five rounds repeat to
+        // 0.2 %), the fewest groups, then the fastest. At 16 x 512 x 512 x 49 eight groups take
+        // 845 us a step against 853 unsplit, which 1 % did not tell apart.
         size_t pick_i = 0;
         for (size_t ci = 0; ci < n_panel; ++ci) {
-            if (med[ci] < 0.0f || med[ci] > 1.01f * best) continue;
-            if (med[pick_i] < 0.0f || med[pick_i] > 1.01f * best || cand[ci].kg < cand[pick_i].kg ||
+            if (med[ci] < 0.0f || med[ci] > 1.005f * best) continue;
+            if (med[pick_i] < 0.0f || med[pick_i] > 1.005f * best || cand[ci].kg < cand[pick_i].kg ||
                 (cand[ci].kg == cand[pick_i].kg && med[ci] < med[pick_i]))
                 pick_i = ci;
         }
