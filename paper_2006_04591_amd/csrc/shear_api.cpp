@@ -1186,7 +1186,7 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     // (rows % 16 == 0 and cols % 128 == 0: at least 8 such tiles)
     const int G = (int)std::min<size_t>(pix / (8 * 32), 2 * (size_t)std::max(4, s->cus)) / 8 * 8;
     const size_t part_stride = (size_t)std::max({32 * 9 * cpo + 32, c3 * 9 * 32 + c3, 32 * 9 * 32 + 32});
-    // workspace: scale | h1 | h2 | d o | dh2 | dh1 | transposed W3 | transposed W2 | partials
+    // workspace: scale | h1 | h2 | d o | dh2 | dh1 | z | transposed W3 | transposed W2 | partials | loss partials
     size_t off = 0;
     const size_t o_sc = off;
     off = al256(off + (size_t)batch * K * 4);
@@ -1208,6 +1208,9 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     off = al256(off + (size_t)32 * 9 * 32 * 2);
     const size_t o_part = off;
     off = al256(off + (size_t)G * part_stride * 4);
+    const size_t o_lp = off;  // the loss of each 8 x 32 tile
+    const int ntiles = (int)(pix / (8 * 32));
+    off = al256(off + (size_t)ntiles * 4);
     if ((rc = ensure_ws2(s, off)) != SHEAR_OK) return rc;
     char* w = (char*)s->ws2;
     float* scale = (float*)(w + o_sc);
@@ -1227,7 +1230,6 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     const shear::ShrinkLayout L = shear::shrink_layout(K);
     const char* pk = (const char*)packed;
     hipError_t e;
-    if ((e = shear::launch_zero_u32((unsigned*)loss, 1, st)) != hipSuccess) return hip_fail(e, "loss reset");
     if ((e = shear::launch_inv_scale(sigma, s->rms_dev, scale, batch, K, st)) != hipSuccess) return hip_fail(e, "scale");
     if ((e = shear::launch_pack_z(c_noisy, scale, zp, K, N, M, batch, st)) != hipSuccess) return hip_fail(e, "z packing");
     // forward: h1, h2 (as in inference), then the loss epilogue of the last layer
@@ -1256,11 +1258,12 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     a.out_bf = dO;
     a.coef = c_noisy;
     a.coef2 = c_clean;
-    a.loss = loss;
+    a.loss = (float*)(w + o_lp);
     a.loss_scale = (float)(1.0 / ((double)batch * (K - 1 > 0 ? K - 1 : 1) * N * M));
     a.temperature = temperature;
     a.cout = K;
     if ((e = shear::launch_conv(3, K, a, batch, st)) != hipSuccess) return hip_fail(e, "layer 3 (loss)");
+    if ((e = shear::launch_loss_sum(a.loss, ntiles, a.loss_scale, loss, st)) != hipSuccess) return hip_fail(e, "loss sum");
     // backward: dW3, dh2, dW2, dh1, dW1
     shear::WgradArgs g{};
     g.batch = batch;

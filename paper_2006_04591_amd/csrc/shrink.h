@@ -29,7 +29,7 @@ struct ConvArgs {
     // training
     const float* coef2;                // layer 2 training: coefficients of the clean images
     const unsigned short* mask_act;    // backward data: saved activation whose relu mask applies
-    float* loss;                       // layer 2 training: sum of squared residuals (added)
+    float* loss;                       // layer 2 training: each 8 x 32 tile's sum of squared residuals
     float loss_scale, temperature;
     int cus;  // compute units of the device (grid of the persistent first layer)
 };
@@ -69,6 +69,8 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
 hipError_t launch_wgrad(int layer, int K, const WgradArgs& a, int blocks, hipStream_t st);
 hipError_t launch_wgrad_reduce(const float* part, float* dW, float* db, int nblk, int cout, int cin, int coutp, int cinp,
                                hipStream_t st);
+// loss = scale x the sum of the n tiles' squared residuals
+hipError_t launch_loss_sum(const float* part, int n, float scale, float* loss, hipStream_t st);
 hipError_t launch_pack_weights_t(const float* W, unsigned short* out, int cout, int cin, int rows, int cols,
                                  hipStream_t st);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, float b1, float b2, float eps,
