@@ -1231,7 +1231,6 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     const char* pk = (const char*)packed;
     hipError_t e;
     if ((e = shear::launch_inv_scale(sigma, s->rms_dev, scale, batch, K, st)) != hipSuccess) return hip_fail(e, "scale");
-    if ((e = shear::launch_pack_z(c_noisy, scale, zp, K, N, M, batch, st)) != hipSuccess) return hip_fail(e, "z packing");
     // forward: h1, h2 (as in inference), then the loss epilogue of the last layer
     shear::ConvArgs a{};
     a.N = N;
@@ -1239,7 +1238,8 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     a.scale = scale;
     a.lowpass = K - 1;
     a.cus = s->cus;
-    a.in = zp;
+    a.coef = c_noisy;
+    a.z = zp;
     a.W = (const unsigned short*)(pk + L.w1);
     a.bias = (const float*)(pk + L.b1);
     a.out_bf = h1;
@@ -1256,7 +1256,6 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     a.W = (const unsigned short*)(pk + L.w3);
     a.bias = (const float*)(pk + L.b3);
     a.out_bf = dO;
-    a.coef = c_noisy;
     a.coef2 = c_clean;
     a.loss = (float*)(w + o_lp);
     a.loss_scale = (float)(1.0 / ((double)batch * (K - 1 > 0 ? K - 1 : 1) * N * M));
@@ -1278,6 +1277,7 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
         return hip_fail(e, "dW3 reduce");
     if ((e = shear::launch_pack_weights_t(params + pW3, t3, K, 32, 32, cpo, st)) != hipSuccess) return hip_fail(e, "W3^T");
     shear::ConvArgs bd{};
+    bd.cus = s->cus;
     bd.N = N;
     bd.M = M;
     bd.in = dO;

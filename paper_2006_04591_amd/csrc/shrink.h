@@ -7,9 +7,8 @@
 
 namespace shear {
 
-// One 3x3 layer launch. Every layer reads bfloat16 channel-last input: the
-// packed z [b][y][x][shrink_cinp(K)] (launch_pack_z) for layer 0, hidden
-// activations [b][y][x][32] for layers 1 and 2. Layers 0 and 1 write
+// One 3x3 layer launch. Layer 0 reads the FP32 coefficients, layers 1 and 2
+// bfloat16 channel-last activations [b][y][x][32]. Layers 0 and 1 write
 // relu(conv + bias) as bfloat16 channel-last activations (out_bf); layer 2
 // writes the shrunk FP32 coefficients out_f (coef kept where
 // |coef * scale| >= softplus(conv + bias), plane `lowpass` kept whole) and,
@@ -27,11 +26,12 @@ struct ConvArgs {
     int cin, cout;            // real channel counts (K for the coefficient side)
     int lowpass;
     // training
+    void* z;                           // layer 0 training: the normalised bfloat16 input, written
     const float* coef2;                // layer 2 training: coefficients of the clean images
     const unsigned short* mask_act;    // backward data: saved activation whose relu mask applies
     float* loss;                       // layer 2 training: each 8 x 32 tile's sum of squared residuals
     float loss_scale, temperature;
-    int cus;  // compute units of the device (grid of the persistent first layer)
+    int cus;  // compute units of the device (grid of the persistent layers)
 };
 
 // Weight-gradient launch: dy bf16 channel-last with dy_ch channels; input x bf16 channel-last (the packed z
@@ -58,12 +58,10 @@ ShrinkLayout shrink_layout(int K);
 hipError_t launch_shrink_pack(int K, const float* W1, const float* b1, const float* W2, const float* b2,
                               const float* W3, const float* b3, void* packed, hipStream_t st);
 hipError_t launch_inv_scale(const float* sigma, const float* rms, float* out, int B, int K, hipStream_t st);
-// z = bf16(c x scale) as channel-last [b][y][x][shrink_cinp(K)], zero padded (M a multiple of 32)
-hipError_t launch_pack_z(const float* c, const float* scale, unsigned short* z, int K, int N, int M, int batch,
-                         hipStream_t st);
-// layer 0, 1, 2: inference layers; 3: last layer with the training epilogue; 4: backward data from 32
-// gradient channels; 5: backward data from shrink_cinp(K) gradient channels; 6: layer 0 with its input
-// staged straight from the FP32 coefficients (coef, scale, cin = K) instead of the packed z.
+// layer 0 of training and 6 of inference: layer 1 of the network, its input staged straight from the FP32
+// coefficients (coef, scale, cin = K) as z = bf16(c x scale); layer 0 also writes z, channel-last
+// [b][y][x][shrink_cinp(K)], zero padded. 1: the hidden layer; 2: the shrink layer; 3: the last layer with
+// the training epilogue; 4: backward data from 32 gradient channels; 5: from shrink_cinp(K).
 hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream_t st);
 // weight gradients of layer 0, 1 or 2 (partials of `blocks` blocks, a multiple of 8; N % 8 == 0, M % 32 == 0)
 hipError_t launch_wgrad(int layer, int K, const WgradArgs& a, int blocks, hipStream_t st);

@@ -59,18 +59,11 @@ struct Pix {
     static constexpr int value = CINP + 8;  // bf16 per staged pixel: 16 bytes of padding against bank conflicts
 };
 
-// LDS of a conv block: the staged input tile; the bf16 output tile (the 32 hidden channels, or the
-// padded gradient planes of layer 2's training epilogue) reuses it once the products are done.
-// The shrink epilogue (MODE 2, 5) works from registers.
-// Input channels are staged at most 32 at a time (a layer with 64 input channels stages and
-// multiplies twice), which keeps the tile at 27 KB.
-template <int CINP>
-constexpr int staged_ch() {
-    return CINP > 32 ? 32 : CINP;
-}
+// LDS of a conv block: the staged input tile; the padded gradient planes of the last layer's training
+// epilogue reuse it once the products are done. The shrink epilogue (MODE 2, 5) works from registers.
 template <int CINP, int OUTC, int MODE>
 constexpr size_t conv_lds_bytes() {
-    constexpr size_t in = (size_t)HH * HW * Pix<staged_ch<CINP>()>::value * 2, out = (size_t)TH * TW * OUTC * 2;
+    constexpr size_t in = (size_t)HH * HW * Pix<CINP>::value * 2, out = (size_t)TH * TW * OUTC * 2;
     return (MODE == 2 || MODE == 5 || in >= out) ? in : out;
 }
 
@@ -97,14 +90,13 @@ __device__ __forceinline__ void gate_loss(float o, float z, float zc, const Gate
     v = gl.c * r * zg * (1.0f - g) * so;
 }
 
-// Stages the halo tile of one image, channels cb .. cb + CS - 1, from bfloat16 channel-last
-// activations with CIN channels per pixel.
-template <int CIN, int CS>
-__device__ __forceinline__ void stage(const ConvArgs& a, unsigned short* s, int b, int y0, int x0, int cb) {
-    constexpr int PIX = Pix<CS>::value;
+// Stages the halo tile of one image from bfloat16 channel-last activations with C channels per pixel.
+template <int C>
+__device__ __forceinline__ void stage(const ConvArgs& a, unsigned short* s, int b, int y0, int x0) {
+    constexpr int PIX = Pix<C>::value;
     const int N = a.N, M = a.M;
     const uint4* in = reinterpret_cast<const uint4*>(a.in);
-    constexpr int CH = CS / 8, CHI = CIN / 8;  // 16-byte chunks per staged / input pixel
+    constexpr int CH = C / 8;  // 16-byte chunks per pixel
     constexpr int TOTAL = HH * HW * CH, NIT = (TOTAL + THREADS - 1) / THREADS;
     // all of a thread's loads are issued before its first LDS store, so that they are in flight
     // together (one load, wait and store at a time left each wavefront waiting on memory latency)
@@ -116,7 +108,7 @@ __device__ __forceinline__ void stage(const ConvArgs& a, unsigned short* s, int 
         if (i < TOTAL) {
             const int ch = i % CH, p = i / CH, xx = p % HW, yy = p / HW;
             const int y = (y0 + yy - 1 + N) & (N - 1), x = (x0 + xx - 1 + M) & (M - 1);
-            v[j] = in[(((size_t)b * N + y) * M + x) * CHI + cb / 8 + ch];
+            v[j] = in[(((size_t)b * N + y) * M + x) * CH + ch];
         }
     }
 #pragma unroll
@@ -138,31 +130,6 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
     return make_uint2(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi));
 }
 
-// z = bf16(coefficients x scale), channel-first FP32 -> channel-last bf16 [b][y][x][CINP] (zero padded):
-// one block per ZW pixels of one row (512-byte runs of each plane), transposed through LDS.
-constexpr int ZW = 128;
-
-template <int CINP>
-__global__ __launch_bounds__(THREADS) void k_pack_z(const float* __restrict__ c, const float* __restrict__ scale,
-                                                 unsigned short* __restrict__ z, int K, int N, int M) {
-    constexpr int PITCH = CINP + 8;
-    __shared__ __attribute__((aligned(16))) unsigned short t[ZW * PITCH];
-    const int xb = M / ZW;
-    const int x0 = (blockIdx.x % xb) * ZW, y = (blockIdx.x / xb) % N, b = blockIdx.x / (xb * N);
-    for (int i = threadIdx.x; i < CINP * ZW; i += THREADS) {
-        const int px = i % ZW, k = i / ZW;
-        float v = 0.0f;
-        if (k < K) v = c[(((size_t)b * K + k) * N + y) * M + x0 + px] * scale[b * K + k];
-        t[px * PITCH + k] = f2bf(v);
-    }
-    __syncthreads();
-    uint4* out = reinterpret_cast<uint4*>(z + (((size_t)b * N + y) * M + x0) * CINP);
-    for (int i = threadIdx.x; i < ZW * CINP / 8; i += THREADS) {
-        const int ch = i % (CINP / 8), px = i / (CINP / 8);
-        out[i] = *reinterpret_cast<const uint4*>(t + px * PITCH + ch * 8);
-    }
-}
-
 template <int NT>
 __device__ __forceinline__ void zero_acc(f32x4 (&acc)[4][NT]) {
 #pragma unroll
@@ -172,21 +139,18 @@ __device__ __forceinline__ void zero_acc(f32x4 (&acc)[4][NT]) {
 }
 
 // out[pixel][co] accumulators of a wavefront: 4 m-tiles (16 pixels of one row) x NT n-tiles, added
-// to acc: output channels co0 .. co0 + COUTP - 1 of the packed weights (CINP input channels per
-// tap), input channels cb .. cb + CS - 1 staged in s.
-template <int CINP, int CS, int COUTP, int PD = 2>
-__device__ __forceinline__ void mma(const ConvArgs& a, const unsigned short* s, f32x4 (&acc)[4][COUTP / 16], int co0,
-                                    int cb) {
-    constexpr int PIX = Pix<CS>::value, NT = COUTP / 16;
+// to acc: output channels co0 .. co0 + COUTP - 1 of the packed weights, CINP input channels staged in s.
+template <int CINP, int COUTP, int PD = 2>
+__device__ __forceinline__ void mma(const ConvArgs& a, const unsigned short* s, f32x4 (&acc)[4][COUTP / 16], int co0) {
+    constexpr int PIX = Pix<CINP>::value, NT = COUTP / 16;
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
     const int lr = l % 16, lk = 8 * (l / 16);
     const unsigned short* W = a.W;
     // steps (tap, 32-channel chunk kc) in order
-    constexpr int KCN = CS / 32, STEPS = 9 * KCN;
+    constexpr int KCN = CINP / 32, STEPS = 9 * KCN;
     auto wfrag = [&](int it, int nt) {
         const int tap = it / KCN, kc = it % KCN;
-        return *reinterpret_cast<const bf16x8*>(W + ((size_t)(co0 + nt * 16 + lr) * 9 + tap) * CINP + cb + kc * 32 +
-                                                lk);
+        return *reinterpret_cast<const bf16x8*>(W + ((size_t)(co0 + nt * 16 + lr) * 9 + tap) * CINP + kc * 32 + lk);
     };
     auto step = [&](int it, const bf16x8(&bf)[NT]) {
         const int tap = it / KCN, kc = it % KCN, dy = tap / 3, dx = tap % 3;
@@ -246,37 +210,21 @@ __device__ __forceinline__ int conv_tile() {
     return (w % 8) * per + w / 8;
 }
 
-// MODE 1: bf16 activations (or the packed z) -> relu -> bf16 activations;
 // MODE 2: activations -> o + b -> shrink of the coefficients where |c scale| >= tau = softplus(o);
 // MODE 5: MODE 2 that also writes tau;
-// MODE 3 (training, last layer): o -> smooth-gate loss (summed into *loss) and its gradient d o, stored as
-//   bf16 channel-last planes [b][y][x][OUTC] (zero beyond K and on the low-pass plane);
-// MODE 4 (training, backward data): gradient planes -> conv with flipped, transposed weights, times the relu
-//   mask of the saved activation (mask_act > 0) -> bf16 gradient activations.
-// Waves per SIMD a conv kernel's registers must allow, where its LDS allows them: the hidden layer
-// holds 5 blocks per CU by its LDS (27 KB); the prefetched weight fragments would otherwise cost it
-// a wave.
-template <int CINP, int MODE>
-constexpr int conv_min_waves() {
-    return (MODE == 1 && CINP == 32) ? 5 : 1;
-}
-
+// MODE 3 (training, last layer): o -> smooth-gate loss (each tile's sum to loss[tile]) and its gradient d o,
+//   stored as bf16 channel-last planes [b][y][x][OUTC] (zero beyond COUTP and on the low-pass plane).
 template <int CINP, int COUTP, int MODE, int OUTC = 32>
-__global__ __launch_bounds__(THREADS, (conv_min_waves<CINP, MODE>())) void k_conv3x3(ConvArgs a) {
+__global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
     constexpr int NT = COUTP / 16;
     extern __shared__ unsigned short smem[];
     unsigned short* s_in = smem;
     const int tx = a.M / TW, ty = a.N / TH, tile = conv_tile();
     const int bx = tile % tx, by = (tile / tx) % ty, b = tile / (tx * ty);
     const int x0 = bx * TW, y0 = by * TH;
-    constexpr int CS = staged_ch<CINP>();
-    static_assert((MODE != 2 && MODE != 5) || CS == CINP, "the shrink layer stages its whole input once");
-    auto stage_part = [&](int cb) { stage<CINP, CS>(a, s_in, b, y0, x0, cb); };
     constexpr bool SHRINK = (MODE == 2 || MODE == 5);
-    if constexpr (SHRINK) {
-        stage_part(0);
-        __syncthreads();
-    }
+    stage<CINP>(a, s_in, b, y0, x0);
+    __syncthreads();
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
     const int lr = l % 16, lm = 4 * (l / 16);
     if constexpr (SHRINK) {
@@ -326,7 +274,7 @@ __global__ __launch_bounds__(THREADS, (conv_min_waves<CINP, MODE>())) void k_con
         }
         f32x4 acc[4][NG];
         zero_acc(acc);
-        mma<CINP, CS, CG, 0>(a, s_in, acc, c0, 0);
+        mma<CINP, CG, 0>(a, s_in, acc, c0);
 #pragma unroll
         for (int nt = 0; nt < NG; ++nt) {
             const int k = c0 + nt * 16 + lr;
@@ -371,21 +319,14 @@ __global__ __launch_bounds__(THREADS, (conv_min_waves<CINP, MODE>())) void k_con
     } else {
         f32x4 acc[4][NT];
         zero_acc(acc);
-#pragma unroll 1
-        for (int cb = 0; cb < CINP; cb += CS) {
-            if (cb > 0) __syncthreads();  // every wave is done with the previous part
-            stage_part(cb);
-            __syncthreads();
-            mma<CINP, CS, COUTP>(a, s_in, acc, 0, cb);
-        }
+        mma<CINP, COUTP>(a, s_in, acc, 0);
         // bf16 results through LDS, then 16-byte channel-last stores of OUTC channels per pixel;
         // the output tile overwrites the staged input once every wave is done reading it
         unsigned short* s_out = smem;
         __syncthreads();
-        [[maybe_unused]] __shared__ float s_loss[MODE == 3 ? THREADS / 64 : 1];
-        [[maybe_unused]] float lsum = 0.0f;
-        [[maybe_unused]] GateLoss gl{};
-        if constexpr (MODE == 3) gl = {1.44269504088896341f / a.temperature, -2.0f * a.loss_scale / a.temperature};
+        __shared__ float s_loss[THREADS / 64];
+        float lsum = 0.0f;
+        const GateLoss gl = {1.44269504088896341f / a.temperature, -2.0f * a.loss_scale / a.temperature};
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             const int prow = (2 * w + mt / 2) * TW + (mt % 2) * 16 + lm;
@@ -393,26 +334,15 @@ __global__ __launch_bounds__(THREADS, (conv_min_waves<CINP, MODE>())) void k_con
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const int co = nt * 16 + lr;
-                float v[4];
-                if constexpr (MODE == 3) {
-                    v[0] = v[1] = v[2] = v[3] = 0.0f;
-                    if (co < a.cout && co != a.lowpass) {
-                        const size_t off = (((size_t)b * a.cout + co) * a.N + y) * a.M + x;
-                        const float4 cn = *reinterpret_cast<const float4*>(a.coef + off);
-                        const float4 cc = *reinterpret_cast<const float4*>(a.coef2 + off);
-                        const float sc = a.scale[b * a.cout + co], bias = a.bias[co];
-                        const float n4[4] = {cn.x, cn.y, cn.z, cn.w}, c4[4] = {cc.x, cc.y, cc.z, cc.w};
+                float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (co < a.cout && co != a.lowpass) {
+                    const size_t off = (((size_t)b * a.cout + co) * a.N + y) * a.M + x;
+                    const float4 cn = *reinterpret_cast<const float4*>(a.coef + off);
+                    const float4 cc = *reinterpret_cast<const float4*>(a.coef2 + off);
+                    const float sc = a.scale[b * a.cout + co], bias = a.bias[co];
+                    const float n4[4] = {cn.x, cn.y, cn.z, cn.w}, c4[4] = {cc.x, cc.y, cc.z, cc.w};
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) gate_loss(acc[mt][nt][i] + bias, n4[i] * sc, c4[i] * sc, gl, lsum, v[i]);
-                    }
-                } else if constexpr (MODE == 4) {
-                    const unsigned short* h = a.mask_act + (((size_t)b * a.N + y) * a.M + x) * 32 + co;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = (bf2f(h[(size_t)i * 32]) > 0.0f) ? acc[mt][nt][i] : 0.0f;
-                } else {
-                    const float bias = a.bias[co];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[mt][nt][i] + bias, 0.0f);
+                    for (int i = 0; i < 4; ++i) gate_loss(acc[mt][nt][i] + bias, n4[i] * sc, c4[i] * sc, gl, lsum, v[i]);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s_out[(prow + i) * OUTC + co] = f2bf(v[i]);
@@ -422,15 +352,12 @@ __global__ __launch_bounds__(THREADS, (conv_min_waves<CINP, MODE>())) void k_con
             for (int i = threadIdx.x; i < TH * TW * (OUTC - COUTP); i += THREADS)
                 s_out[(i / (OUTC - COUTP)) * OUTC + COUTP + i % (OUTC - COUTP)] = 0;
         }
-        if constexpr (MODE == 3) {
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
-            if (l == 0) s_loss[w] = lsum;
-        }
+        for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+        if (l == 0) s_loss[w] = lsum;
         __syncthreads();
-        if constexpr (MODE == 3) {  // the tile's squared residuals, summed over tiles by k_loss_sum
-            if (threadIdx.x == 0) a.loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
-        }
+        // the tile's squared residuals, summed over tiles by k_loss_sum
+        if (threadIdx.x == 0) a.loss[tile] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
         constexpr int CH = OUTC / 8;
         uint4* out = reinterpret_cast<uint4*>(a.out_bf);
         for (int i = threadIdx.x; i < TH * TW * CH; i += THREADS) {
@@ -558,38 +485,40 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
     }
 }
 
-// Staged rows R0 .. R0 + NR - 1 of a tile's hidden activations with the halo columns, [pixel][32
-// channels] bf16, in 16-byte units.
-template <int NR>
+// Staged rows R0 .. R0 + NR - 1 of a tile's channel-last bf16 input (hidden activations or gradients, C
+// channels) with the halo columns, in 16-byte units.
+template <int NR, int C = 32>
 struct HidRegs {
-    static constexpr int TOTAL = NR * PHW * 4, NIT = (TOTAL + PTHREADS - 1) / PTHREADS;
+    static constexpr int U = C / 8, TOTAL = NR * PHW * U, NIT = (TOTAL + PTHREADS - 1) / PTHREADS;
     uint4 v[NIT];
 };
 
-template <int NR>
-__device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR>& r, int b, int y0, int x0, int R0) {
+template <int NR, int C = 32>
+__device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR, C>& r, int b, int y0, int x0, int R0) {
+    using R = HidRegs<NR, C>;
     const int N = a.N, M = a.M;
     const uint4* in = reinterpret_cast<const uint4*>(a.in);
 #pragma unroll
-    for (int j = 0; j < HidRegs<NR>::NIT; ++j) {
+    for (int j = 0; j < R::NIT; ++j) {
         const int i = (int)threadIdx.x + j * PTHREADS;
         r.v[j] = make_uint4(0u, 0u, 0u, 0u);
-        if (i < HidRegs<NR>::TOTAL) {
-            const int ch = i % 4, p = i / 4, xx = p % PHW, yy = R0 + p / PHW;
+        if (i < R::TOTAL) {
+            const int ch = i % R::U, p = i / R::U, xx = p % PHW, yy = R0 + p / PHW;
             const int y = (y0 + yy - 1 + N) & (N - 1), x = (x0 + xx - 1 + M) & (M - 1);
-            r.v[j] = in[(((size_t)b * N + y) * M + x) * 4 + ch];
+            r.v[j] = in[(((size_t)b * N + y) * M + x) * R::U + ch];
         }
     }
 }
 
-template <int NR>
-__device__ __forceinline__ void hid_store(const HidRegs<NR>& r, unsigned short* s, int R0) {
-    constexpr int PIX = Pix<32>::value;
+template <int NR, int C = 32>
+__device__ __forceinline__ void hid_store(const HidRegs<NR, C>& r, unsigned short* s, int R0) {
+    using R = HidRegs<NR, C>;
+    constexpr int PIX = Pix<C>::value;
 #pragma unroll
-    for (int j = 0; j < HidRegs<NR>::NIT; ++j) {
+    for (int j = 0; j < R::NIT; ++j) {
         const int i = (int)threadIdx.x + j * PTHREADS;
-        if (i < HidRegs<NR>::TOTAL) {
-            const int ch = i % 4, p = i / 4;
+        if (i < R::TOTAL) {
+            const int ch = i % R::U, p = i / R::U;
             *reinterpret_cast<uint4*>(s + (R0 * PHW + p) * PIX + ch * 8) = r.v[j];
         }
     }
@@ -613,36 +542,51 @@ __device__ __forceinline__ void xcd_chunk(int ntiles, int& first, int& end) {
     end = (int)(lo + ((hi - lo) * (j + 1)) / per);
 }
 
-// FROM_COEF: the first layer (input: the FP32 coefficient planes, normalised and rounded on staging);
-// else the hidden layer (input: the bf16 activations of the first, CINP = 32).
+// the bf16 of v where the bf16 of m (a saved activation, never NaN) is > 0, else 0
+__device__ __forceinline__ uint4 positive_only(uint4 v, uint4 m) {
+    auto f = [](unsigned x, unsigned y) {
+        return x & (((int)(y << 16) > 0 ? 0xFFFFu : 0u) | ((int)y > 0xFFFF ? 0xFFFF0000u : 0u));
+    };
+    return make_uint4(f(v.x, m.x), f(v.y, m.y), f(v.z, m.z), f(v.w, m.w));
+}
+
+// COEF_RELU: the first layer (input: the FP32 coefficient planes, normalised and rounded on staging);
+// COEF_RELU_Z: the first layer in training, which also writes the staged input z (bf16, channel-last, CINP
+// channels) for the weight gradient; HID_RELU: the hidden layer (input: the bf16 activations of the
+// first, CINP = 32); GRAD_MASK: backward data (input: gradient planes; flipped, transposed weights; the
+// output is masked by relu's derivative, mask_act > 0, as it leaves).
 // The first layer walks its block's chunk of tiles down vertical strips (tile index: rows of tiles
 // fastest, then strips of 64 columns, then images), as a sliding window: the staged tile's last two
 // rows (its bottom halo and last row) are the next tile's first two, so they move up in LDS and
 // only 8 new rows are loaded per tile (10 at the top of a strip); neighbouring chunks of an XCD run
 // down neighbouring strips together, so the halo columns hit that XCD's L2 (0.449 -> 0.406 ms).
-// The hidden layer, whose tiles are a quarter of the bytes, takes its tiles interleaved over the
-// XCD's blocks and loads all 10 rows (the sliding window's extra barrier and copy made it slower:
-// 0.123 -> 0.138 ms).
-template <int CINP, bool FROM_COEF>
-__global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvArgs a, int ntiles) {
+// The other layers, whose tiles are a quarter or half of the bytes, take their tiles interleaved over
+// the XCD's blocks and load all 10 rows (the sliding window's extra barrier and copy made the hidden
+// layer slower: 0.123 -> 0.138 ms).
+// In a training step at 16 x 512^2 x 49, z and the first layer took 0.33 + 0.40 ms as a packing pass and
+// a layer of one-tile blocks, and the backward data of the last and the hidden layer 0.41 and 0.18 ms as
+// one-tile blocks; here 0.52, 0.27 and 0.14 ms.
+enum ConvKind { COEF_RELU, COEF_RELU_Z, HID_RELU, GRAD_MASK };
+template <int CINP, ConvKind KIND>
+__global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) void k_conv_relu(ConvArgs a, int ntiles) {
+    constexpr bool FROM_COEF = KIND == COEF_RELU || KIND == COEF_RELU_Z;
     constexpr int CS = CINP, PIX = Pix<CS>::value, WP = PLds<CS>::WP, KCN = CS / 32, STEPS = 9 * KCN;
-    static_assert(FROM_COEF || CINP == 32, "the hidden layer has 32 input channels");
     constexpr bool SLIDE = FROM_COEF;
     constexpr int R0 = SLIDE ? 2 : 0, NR = PHH - R0;  // staged rows loaded per tile (the prefetch)
-    using Regs8 = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR>>::type;
-    using Regs2 = typename std::conditional<FROM_COEF, CoefRegs<CS, 2>, HidRegs<2>>::type;
+    using Regs8 = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR, CS>>::type;
+    using Regs2 = typename std::conditional<FROM_COEF, CoefRegs<CS, 2>, HidRegs<2, CS>>::type;
     auto load8 = [&](Regs8& r, int b, int y0, int x0) {  // staged rows R0 .. 9
         if constexpr (FROM_COEF) {
             coef_load<CS, NR>(a, r, b, y0, x0, R0);
         } else {
-            hid_load<NR>(a, r, b, y0, x0, R0);
+            hid_load<NR, CS>(a, r, b, y0, x0, R0);
         }
     };
     auto store8 = [&](const Regs8& r, unsigned short* s) {
         if constexpr (FROM_COEF) {
             coef_store<CS, NR>(r, s, R0);
         } else {
-            hid_store<NR>(r, s, R0);
+            hid_store<NR, CS>(r, s, R0);
         }
     };
     auto stage_top = [&](unsigned short* s, int b, int y0, int x0) {  // staged rows 0, 1 straight from memory
@@ -651,8 +595,8 @@ __global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvA
             coef_load<CS, 2>(a, r2, b, y0, x0, 0);
             coef_store<CS, 2>(r2, s, 0);
         } else {
-            hid_load<2>(a, r2, b, y0, x0, 0);
-            hid_store<2>(r2, s, 0);
+            hid_load<2, CS>(a, r2, b, y0, x0, 0);
+            hid_store<2, CS>(r2, s, 0);
         }
     };
     extern __shared__ unsigned short smem[];
@@ -686,9 +630,16 @@ __global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvA
     }
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
     const int lr = l % 16, lm = 4 * (l / 16), lk = 8 * (l / 16);
-    float bias[2];
+    [[maybe_unused]] float bias[2];
+    if constexpr (KIND != GRAD_MASK) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) bias[nt] = a.bias[nt * 16 + lr];
+        for (int nt = 0; nt < 2; ++nt) bias[nt] = a.bias[nt * 16 + lr];
+    }
+    constexpr int OU = PTH * PTW * 4 / PTHREADS;  // 16-byte units of the output tile per thread
+    auto out_unit = [&](int j, int b, int y0, int x0) {
+        const int i = (int)threadIdx.x + j * PTHREADS, ch = i % 4, p = i / 4;
+        return (((size_t)b * a.N + y0 + p / PTW) * a.M + x0 + p % PTW) * 4 + ch;
+    };
     Regs8 r;
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
@@ -702,12 +653,25 @@ __global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvA
     }
     __syncthreads();
     for (;;) {
+        if constexpr (KIND == COEF_RELU_Z) {  // the staged tile without its halo
+            constexpr int ZU = CS / 8;
+            uint4* z = reinterpret_cast<uint4*>(a.z);
+#pragma unroll
+            for (int j = 0; j < PTH * PTW * ZU / PTHREADS; ++j) {
+                const int i = (int)threadIdx.x + j * PTHREADS, ch = i % ZU, p = i / ZU, px = p % PTW, py = p / PTW;
+                z[(((size_t)b * a.N + y0 + py) * a.M + x0 + px) * ZU + ch] =
+                    *reinterpret_cast<const uint4*>(s_in + ((py + 1) * PHW + px + 1) * PIX + ch * 8);
+            }
+        }
         // wave w: tile row w, 4 m-tiles of 16 pixels
         f32x4 acc[4][2];
         zero_acc(acc);
 #pragma unroll 1
         for (int it = 0; it < STEPS; ++it) {
-            const int tap = it / KCN, kc = it % KCN, dy = tap / 3, dx = tap % 3;
+            // inference takes each tap's channels together, training all taps of 32 channels at a time
+            constexpr bool TAP_MAJOR = KIND == COEF_RELU || KIND == HID_RELU;
+            const int tap = TAP_MAJOR ? it / KCN : it % 9, kc = TAP_MAJOR ? it % KCN : it / 9;
+            const int dy = tap / 3, dx = tap % 3;
             bf16x8 bf[2];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
@@ -721,8 +685,13 @@ __global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvA
                     acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr, bf[nt], acc[mt][nt], 0, 0, 0);
             }
         }
+        [[maybe_unused]] uint4 mk[OU];
+        if constexpr (KIND == GRAD_MASK) {  // in flight while the outputs pass through LDS (earlier, they spill)
+#pragma unroll
+            for (int j = 0; j < OU; ++j) mk[j] = reinterpret_cast<const uint4*>(a.mask_act)[out_unit(j, b, y0, x0)];
+        }
         __syncthreads();  // every wave is done reading the staged tile
-        // relu(acc + bias) -> bf16 output tile [pixel][32 channels]
+        // relu(acc + bias), or the gradient -> bf16 output tile [pixel][32 channels]
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             const int prow = w * PTW + 16 * mt + lm;
@@ -730,11 +699,17 @@ __global__ __launch_bounds__(PTHREADS, FROM_COEF ? 2 : 4) void k_conv_relu(ConvA
             for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    s_out[(prow + i) * 32 + nt * 16 + lr] = f2bf(fmaxf(acc[mt][nt][i] + bias[nt], 0.0f));
+                    s_out[(prow + i) * 32 + nt * 16 + lr] =
+                        f2bf(KIND == GRAD_MASK ? acc[mt][nt][i] : fmaxf(acc[mt][nt][i] + bias[nt], 0.0f));
         }
         __syncthreads();  // the output tile is written
-        {
-            uint4* out = reinterpret_cast<uint4*>(a.out_bf);
+        uint4* out = reinterpret_cast<uint4*>(a.out_bf);
+        if constexpr (KIND == GRAD_MASK) {
+#pragma unroll
+            for (int j = 0; j < OU; ++j)
+                out[out_unit(j, b, y0, x0)] =
+                    positive_only(*reinterpret_cast<const uint4*>(s_out + ((int)threadIdx.x + j * PTHREADS) * 8), mk[j]);
+        } else {
             for (int i = (int)threadIdx.x; i < PTH * PTW * 4; i += PTHREADS) {
                 const int ch = i % 4, p = i / 4, px = p % PTW, py = p / PTW;
                 out[(((size_t)b * a.N + y0 + py) * a.M + x0 + px) * 4 + ch] =
@@ -1228,17 +1203,17 @@ hipError_t conv_t(const ConvArgs& a, int batch, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int CINP, bool FROM_COEF>
+template <int CINP, ConvKind KIND>
 hipError_t conv_relu_t(const ConvArgs& a, int batch, hipStream_t st) {
-    const void* fn = reinterpret_cast<const void*>(&k_conv_relu<CINP, FROM_COEF>);
+    const void* fn = reinterpret_cast<const void*>(&k_conv_relu<CINP, KIND>);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PLds<CINP>::bytes);
     if (e != hipSuccess) return e;
     const int ntiles = batch * (a.N / PTH) * (a.M / PTW);
-    // blocks per CU its registers and LDS allow (first layer: 187 VGPRs, 132 KB; hidden layer: 106
-    // VGPRs, 72 KB), a multiple of the 8 XCDs
-    const int blocks = (FROM_COEF ? 1 : 2) * std::max(8, a.cus / 8 * 8);
-    hipLaunchKernelGGL((k_conv_relu<CINP, FROM_COEF>), dim3((unsigned)blocks), dim3(PTHREADS), PLds<CINP>::bytes, st,
-                       a, ntiles);
+    // blocks per CU its registers and LDS allow (64 channels or coefficients: one, 132 KB; 32 bf16
+    // channels: two, 72 KB), a multiple of the 8 XCDs
+    const int blocks = (CINP == 32 && KIND >= HID_RELU ? 2 : 1) * std::max(8, a.cus / 8 * 8);
+    hipLaunchKernelGGL((k_conv_relu<CINP, KIND>), dim3((unsigned)blocks), dim3(PTHREADS), PLds<CINP>::bytes, st, a,
+                       ntiles);
     return hipGetLastError();
 }
 
@@ -1274,7 +1249,7 @@ hipError_t wgrad_t(const WgradArgs& a, int blocks, hipStream_t st) {
 
 int shrink_cinp(int K) { return K <= 32 ? 32 : 64; }
 int shrink_coutp(int K) { return (K + 15) / 16 * 16; }
-bool shrink_supported(int K, int N, int M) { return K >= 1 && K <= 64 && N >= TH && N % TH == 0 && M % ZW == 0; }
+bool shrink_supported(int K, int N, int M) { return K >= 1 && K <= 64 && N >= TH && N % TH == 0 && M % 128 == 0; }
 
 ShrinkLayout shrink_layout(int K) {
     ShrinkLayout L;
@@ -1318,23 +1293,23 @@ hipError_t launch_inv_scale(const float* sigma, const float* rms, float* out, in
 }
 
 hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream_t st) {
-    if (layer == 0) return shrink_cinp(K) == 32 ? conv_t<32, 32, 1>(a, batch, st) : conv_t<64, 32, 1>(a, batch, st);
-    if (layer == 1) return conv_relu_t<32, false>(a, batch, st);  // h1 -> h2 (persistent)
-    if (layer == 6)  // layer 1 staged straight from the coefficients (a.coef, a.scale, a.cin = K)
-        return shrink_cinp(K) == 32 ? conv_relu_t<32, true>(a, batch, st) : conv_relu_t<64, true>(a, batch, st);
+    const bool c32 = shrink_cinp(K) == 32;
+    if (layer == 0) return c32 ? conv_relu_t<32, COEF_RELU_Z>(a, batch, st) : conv_relu_t<64, COEF_RELU_Z>(a, batch, st);
+    if (layer == 1) return conv_relu_t<32, HID_RELU>(a, batch, st);  // h1 -> h2
+    if (layer == 6) return c32 ? conv_relu_t<32, COEF_RELU>(a, batch, st) : conv_relu_t<64, COEF_RELU>(a, batch, st);
     if (layer == 3) {  // training: last layer with the loss epilogue, gradient planes of shrink_cinp(K) channels
         // the low-pass plane, the last, has no loss and a zero gradient: groups of 16 channels up to K - 1
         // (at K = 49 three groups of products and epilogue instead of four)
         switch (std::max(16, shrink_coutp(K - 1))) {
             case 16: return conv_t<32, 16, 3, 32>(a, batch, st);
-            case 32: return shrink_cinp(K) == 32 ? conv_t<32, 32, 3, 32>(a, batch, st) : conv_t<32, 32, 3, 64>(a, batch, st);
+            case 32: return c32 ? conv_t<32, 32, 3, 32>(a, batch, st) : conv_t<32, 32, 3, 64>(a, batch, st);
             case 48: return conv_t<32, 48, 3, 64>(a, batch, st);
             case 64: return conv_t<32, 64, 3, 64>(a, batch, st);
         }
         return hipErrorInvalidValue;
     }
-    if (layer == 4) return conv_t<32, 32, 4>(a, batch, st);  // backward data from 32 gradient channels
-    if (layer == 5) return shrink_cinp(K) == 32 ? conv_t<32, 32, 4>(a, batch, st) : conv_t<64, 32, 4>(a, batch, st);
+    if (layer == 4 || (layer == 5 && c32)) return conv_relu_t<32, GRAD_MASK>(a, batch, st);  // backward data
+    if (layer == 5) return conv_relu_t<64, GRAD_MASK>(a, batch, st);
     if (a.tau) {  // the shrink layer that also writes the thresholds
         switch (shrink_coutp(K)) {
             case 16: return conv_t<32, 16, 5>(a, batch, st);
@@ -1401,16 +1376,5 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, floa
 }  // namespace shear
 
 namespace shear {
-
-hipError_t launch_pack_z(const float* c, const float* scale, unsigned short* z, int K, int N, int M, int batch,
-                         hipStream_t st) {
-    if (M % ZW != 0) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((size_t)batch * N * (M / ZW)));
-    if (shrink_cinp(K) == 32)
-        hipLaunchKernelGGL(k_pack_z<32>, grid, dim3(THREADS), 0, st, c, scale, z, K, N, M);
-    else
-        hipLaunchKernelGGL(k_pack_z<64>, grid, dim3(THREADS), 0, st, c, scale, z, K, N, M);
-    return hipGetLastError();
-}
 
 }  // namespace shear
