@@ -487,20 +487,20 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
 
 // Staged rows R0 .. R0 + NR - 1 of a tile's channel-last bf16 input (hidden activations or gradients, C
 // channels) with the halo columns, in 16-byte units.
-template <int NR, int C = 32>
+template <int NR, int C = 32, int THR = PTHREADS>
 struct HidRegs {
-    static constexpr int U = C / 8, TOTAL = NR * PHW * U, NIT = (TOTAL + PTHREADS - 1) / PTHREADS;
+    static constexpr int U = C / 8, TOTAL = NR * PHW * U, NIT = (TOTAL + THR - 1) / THR;
     uint4 v[NIT];
 };
 
-template <int NR, int C = 32>
-__device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR, C>& r, int b, int y0, int x0, int R0) {
-    using R = HidRegs<NR, C>;
+template <int NR, int C = 32, int THR = PTHREADS>
+__device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR, C, THR>& r, int b, int y0, int x0, int R0) {
+    using R = HidRegs<NR, C, THR>;
     const int N = a.N, M = a.M;
     const uint4* in = reinterpret_cast<const uint4*>(a.in);
 #pragma unroll
     for (int j = 0; j < R::NIT; ++j) {
-        const int i = (int)threadIdx.x + j * PTHREADS;
+        const int i = (int)threadIdx.x + j * THR;
         r.v[j] = make_uint4(0u, 0u, 0u, 0u);
         if (i < R::TOTAL) {
             const int ch = i % R::U, p = i / R::U, xx = p % PHW, yy = R0 + p / PHW;
@@ -510,13 +510,13 @@ __device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR, C>& r, i
     }
 }
 
-template <int NR, int C = 32>
-__device__ __forceinline__ void hid_store(const HidRegs<NR, C>& r, unsigned short* s, int R0) {
-    using R = HidRegs<NR, C>;
+template <int NR, int C = 32, int THR = PTHREADS>
+__device__ __forceinline__ void hid_store(const HidRegs<NR, C, THR>& r, unsigned short* s, int R0) {
+    using R = HidRegs<NR, C, THR>;
     constexpr int PIX = Pix<C>::value;
 #pragma unroll
     for (int j = 0; j < R::NIT; ++j) {
-        const int i = (int)threadIdx.x + j * PTHREADS;
+        const int i = (int)threadIdx.x + j * THR;
         if (i < R::TOTAL) {
             const int ch = i % R::U, p = i / R::U;
             *reinterpret_cast<uint4*>(s + (R0 * PHW + p) * PIX + ch * 8) = r.v[j];
@@ -753,55 +753,60 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 }
 
 // ---------------------------------------------------------------- persistent shrink layer
-// The last layer with the shrink decision (no tau output) in the persistent form of k_conv_relu:
-// one 512-thread block per CU keeps the layer's weights in LDS and walks its XCD's range of
-// 8 x 64-pixel tiles. Per tile, the staged hidden activations serve CG output channels at a time;
-// each pass's FP32 coefficients come into LDS as 256-byte row runs, are decided there in the matrix
-// cores' lane layout (c kept or zeroed in place) and leave as 256-byte row runs. The next pass's
-// coefficients, and during the first pass the next tile's activations, are in flight in registers
-// while the matrix cores work.
-template <int COUTP>
-struct SLds {
-    static constexpr int CG = COUTP <= 32 ? COUTP : (COUTP % 32 == 0 ? 32 : 16);  // channels per pass
-    static constexpr int PIX = Pix<32>::value;
-    static constexpr int WP = 9 * 32 + 8;            // bf16 per output channel of the staged weights
-    static constexpr int CP = PTH * PTW + 4;         // floats per channel of the coefficient pass buffer
-    static constexpr size_t h = (size_t)PHH * PHW * PIX * 2, w = (size_t)COUTP * WP * 2,
-                            c = (size_t)CG * CP * 4;
-    static constexpr size_t bytes = h + w + c;
-};
-
-// One pass's coefficients of tile (b, y0, x0): channels c0 .. c0 + CG - 1 (those below K), 8 rows of
-// 64 pixels, as 16-byte units with 16 lanes per 256-byte row run.
-template <int CG>
-struct PassRegs {
-    static constexpr int TOTAL = CG * PTH * (PTW / 4), NIT = (TOTAL + PTHREADS - 1) / PTHREADS;
-    float4 v[NIT];
-};
-
-template <int CG>
-__device__ __forceinline__ void pass_load(const ConvArgs& a, PassRegs<CG>& r, int b, int y0, int x0, int c0) {
-#pragma unroll
-    for (int j = 0; j < PassRegs<CG>::NIT; ++j) {
-        const int i = (int)threadIdx.x + j * PTHREADS;
-        const int q = i % (PTW / 4), yy = (i / (PTW / 4)) % PTH, kl = i / (PTH * PTW / 4), k = c0 + kl;
-        r.v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (i < PassRegs<CG>::TOTAL && k < a.cout)
-            r.v[j] = *reinterpret_cast<const float4*>(a.coef + (((size_t)b * a.cout + k) * a.N + y0 + yy) * a.M + x0 + 4 * q);
-    }
+// The last layer with the shrink decision (no tau output), persistent: two or three blocks per CU walk their
+// XCD's range of 8 x 64-pixel tiles. A wavefront keeps the weights of one group of 16 output channels in
+// registers (36 VGPRs) and takes PTH / RH rows of the tile: per row, 4 m-tiles of 16 pixels x 9 taps of
+// products out of the staged activations, then the decision on the row's coefficients where the matrix
+// cores leave the outputs (a lane holds 4 consecutive pixels of one channel: 16-byte loads and stores in
+// 64-byte runs, two of them to a line), with the next row's coefficients in flight. Nothing but the
+// activations passes through LDS, and the wavefronts meet only where the staged tile changes (the
+// next tile's activations are in registers by then), so products, decisions and memory overlap freely.
+// The low-pass plane, the last, is kept whole: where it would be alone in its group (K = 17, 33, 49) it
+// is copied and the group's products and decisions are left out. Per 16 x 512^2 x 49 batch: 0.44-0.46 ms;
+// with the coefficients passed through LDS in three barrier phases per 32 channels, one block per CU,
+// 0.50 ms. What bounds it: 1.64 GB of coefficients in and out and 0.35 GB of activations.
+//
+// The decision |c scale| >= tau = softplus(o) is taken without forming tau: with a = |c scale| >= 0,
+// m = max(o, 0), u = e^-|o| in (0, 1] and d = a - m, softplus(o) = m + log1p(u), so a >= softplus(o)
+// <=> expm1(d) >= u. d is clamped to [0, 0.75] (below 0, expm1 < 0 < u; above, expm1 > 1 >= u), where
+// expm1 is its Taylor polynomial of degree 9 (remainder < 2e-8 relative), and for o > 0, u is kept
+// above 1e-30 (beyond o = 87 it underflows: then softplus(o) = o in FP32 and the test is d > 0). The
+// low-pass plane takes o = -inf: u = 0, every coefficient kept. One hardware exponential replaces
+// softplus's exponential, logarithm and reciprocal, with no branch, and the decision keeps softplus's
+// relative precision for small and large thresholds alike.
+__device__ __forceinline__ float shrink_keep(float v, float sc, float o) {
+    constexpr float L2E = 1.44269504088896341f;
+    const float d = fminf(fmaxf(fabsf(v * sc) - fmaxf(o, 0.0f), 0.0f), 0.75f);
+    const float u = fmaxf(__builtin_amdgcn_exp2f(-fabsf(o) * L2E), o > 0.0f ? 1e-30f : 0.0f);
+    float e = 1.0f / 362880.0f;
+    e = fmaf(e, d, 1.0f / 40320.0f);
+    e = fmaf(e, d, 1.0f / 5040.0f);
+    e = fmaf(e, d, 1.0f / 720.0f);
+    e = fmaf(e, d, 1.0f / 120.0f);
+    e = fmaf(e, d, 1.0f / 24.0f);
+    e = fmaf(e, d, 1.0f / 6.0f);
+    e = fmaf(e, d, 0.5f);
+    e = fmaf(e, d, 1.0f);
+    return (e * d >= u) ? v : 0.0f;
 }
 
-template <int COUTP>
-__global__ __launch_bounds__(PTHREADS, 2) void k_conv_shrink(ConvArgs a, int ntiles) {
-    using L = SLds<COUTP>;
-    constexpr int CG = L::CG, NG = CG / 16, NP = COUTP / CG, PIX = L::PIX, WP = L::WP, CP = L::CP;
-    static_assert(COUTP % CG == 0, "the passes cover the padded output channels exactly");
-    constexpr float L2E = 1.44269504088896341f;
+// NG groups of 16 output channels
+template <int NG>
+struct SCfg {
+    static constexpr int RH = NG == 3 ? 2 : 4 / NG;  // parts of the tile's rows
+    static constexpr int ROWS = PTH / RH, WAVES = NG * RH, THREADS = 64 * WAVES;
+    static constexpr int BLOCKS = 12 / WAVES;  // per CU: 12 wavefronts of up to 168 registers
+    static constexpr int PIX = Pix<32>::value;
+    static constexpr size_t LDS = (size_t)PHH * PHW * PIX * 2;
+};
+
+template <int NG>
+__global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs a, int ntiles) {
+    using C = SCfg<NG>;
+    constexpr int PIX = C::PIX, THR = C::THREADS;
+    using H = HidRegs<PHH, 32, THR>;
     extern __shared__ unsigned short smem[];
-    unsigned short* s_h = smem;
-    unsigned short* s_w = smem + L::h / 2;
-    float* s_c = reinterpret_cast<float*>(smem + (L::h + L::w) / 2);
-    const int tx = a.M / PTW, ty = a.N / PTH;
+    const int tx = a.M / PTW, ty = a.N / PTH, K = a.cout;
     int t, end, stride;
     xcd_range(ntiles, t, end, stride);
     if (t >= end) return;  // the whole block: no tile
@@ -810,113 +815,76 @@ __global__ __launch_bounds__(PTHREADS, 2) void k_conv_shrink(ConvArgs a, int nti
         y0 = ((tile / tx) % ty) * PTH;
         b = tile / (tx * ty);
     };
-    // weights [co][tap][ci] (COUTP rows, zero beyond K) -> LDS rows of WP bf16
-    for (int i = (int)threadIdx.x; i < COUTP * 9 * 32 / 8; i += PTHREADS) {
-        const int co = i / (9 * 32 / 8), r = i % (9 * 32 / 8);
-        *reinterpret_cast<uint4*>(s_w + co * WP + 8 * r) = reinterpret_cast<const uint4*>(a.W)[i];
-    }
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), l = threadIdx.x % 64;
     const int lr = l % 16, lk = 8 * (l / 16), lm = 4 * (l / 16);
-    HidRegs<PHH> hr;
-    PassRegs<CG> pr;
+    const int r0 = (w / NG) * C::ROWS;
+    // the lane's channel; lanes beyond the last plane repeat it and do not store
+    const int kc = (w % NG) * 16 + lr, k = min(kc, K - 1);
+    const bool lp_copy = K == 16 * NG + 1;
+    bf16x8 wf[9];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+        wf[tap] = *reinterpret_cast<const bf16x8*>(a.W + ((size_t)kc * 9 + tap) * 32 + lk);
+    const float bias = k == a.lowpass ? -INFINITY : a.bias[k];
+    const size_t plane = (size_t)a.N * a.M;
+    auto row_off = [&](int b, int y0, int x0, int r) { return ((size_t)b * K + k) * plane + (size_t)(y0 + r) * a.M + x0 + lm; };
+    H hr;
+    float4 cv[4];
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
-    hid_load<PHH>(a, hr, b, y0, x0, 0);
-    pass_load<CG>(a, pr, b, y0, x0, 0);
-    hid_store<PHH>(hr, s_h, 0);
-    int tn = t + stride, bn = 0, yn = 0, xn = 0;
-    if (tn < end) tile_origin(tn, bn, yn, xn);
+    hid_load<PHH, 32, THR>(a, hr, b, y0, x0, 0);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) cv[mt] = *reinterpret_cast<const float4*>(a.coef + row_off(b, y0, x0, r0) + 16 * mt);
     for (;;) {
+        hid_store<PHH, 32, THR>(hr, smem, 0);
+        const float sc = a.scale[b * K + k];
+        const int tn = t + stride;
+        int bn = b, yn = y0, xn = x0;
+        if (tn < end) tile_origin(tn, bn, yn, xn);
+        __syncthreads();  // the tile is staged
+        if (tn < end) hid_load<PHH, 32, THR>(a, hr, bn, yn, xn, 0);
+        float4 lp = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const size_t lpo = ((size_t)b * K + K - 1) * plane + (size_t)(y0 + (int)threadIdx.x / 16) * a.M + x0 +
+                           4 * ((int)threadIdx.x % 16);
+        if (lp_copy && threadIdx.x < PTH * PTW / 4) lp = *reinterpret_cast<const float4*>(a.coef + lpo);
 #pragma unroll 1
-        for (int p = 0; p < NP; ++p) {
-            const int c0 = p * CG;
-            // this pass's coefficients -> LDS [channel][row][pixel] (after the previous pass's copy-out
-            // has read the buffer: the barrier at the end of each pass)
+        for (int r = 0; r < C::ROWS; ++r) {
+            f32x4 acc[4];
 #pragma unroll
-            for (int j = 0; j < PassRegs<CG>::NIT; ++j) {
-                const int i = (int)threadIdx.x + j * PTHREADS;
-                if (i < PassRegs<CG>::TOTAL) {
-                    const int q = i % (PTW / 4), yy = (i / (PTW / 4)) % PTH, kl = i / (PTH * PTW / 4);
-                    *reinterpret_cast<float4*>(s_c + kl * CP + yy * PTW + 4 * q) = pr.v[j];
-                }
-            }
-            __syncthreads();  // coefficients (and, in the first pass, the activations) staged
-            // next loads: the following pass's coefficients, or the next tile's first pass and activations
-            if (p + 1 < NP) {
-                pass_load<CG>(a, pr, b, y0, x0, c0 + CG);
-            } else if (tn < end) {
-                hid_load<PHH>(a, hr, bn, yn, xn, 0);
-                pass_load<CG>(a, pr, bn, yn, xn, 0);
-            }
-            f32x4 acc[4][NG];
-            zero_acc(acc);
-#pragma unroll 1
-            for (int tap = 0; tap < 9; ++tap) {
-                const int dy = tap / 3, dx = tap % 3;
-                bf16x8 bf[NG];
+            for (int mt = 0; mt < 4; ++mt) acc[mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            const unsigned short* sr = smem + ((r0 + r) * PHW + lr) * PIX + lk;
 #pragma unroll
-                for (int nt = 0; nt < NG; ++nt)
-                    bf[nt] = *reinterpret_cast<const bf16x8*>(s_w + (c0 + nt * 16 + lr) * WP + tap * 32 + lk);
+            for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt) {
-                    const bf16x8 afr = *reinterpret_cast<const bf16x8*>(s_h + ((w + dy) * PHW + 16 * mt + lr + dx) * PIX + lk);
-#pragma unroll
-                    for (int nt = 0; nt < NG; ++nt)
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr, bf[nt], acc[mt][nt], 0, 0, 0);
+                    const bf16x8 af =
+                        *reinterpret_cast<const bf16x8*>(sr + ((tap / 3) * PHW + 16 * mt + tap % 3) * PIX);
+                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, wf[tap], acc[mt], 0, 0, 0);
                 }
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const float4 c = cv[mt];
+                acc[mt] = f32x4{shrink_keep(c.x, sc, acc[mt][0] + bias), shrink_keep(c.y, sc, acc[mt][1] + bias),
+                                shrink_keep(c.z, sc, acc[mt][2] + bias), shrink_keep(c.w, sc, acc[mt][3] + bias)};
             }
-            // the decision of k_conv3x3's MODE 2, on the staged coefficients, in place
+            // the next row's coefficients, of this tile or the first of the next one, in flight during its
+            // products; issued before this row's stores, so that they need not wait for those
+            const float* cp = a.coef + (r + 1 < C::ROWS ? row_off(b, y0, x0, r0 + r + 1) : row_off(bn, yn, xn, r0));
 #pragma unroll
-            for (int nt = 0; nt < NG; ++nt) {
-                const int kl = nt * 16 + lr, k = c0 + kl;
-                if (k >= a.cout) continue;
-                const bool lowpass = (k == a.lowpass);
-                const float bias = lowpass ? -INFINITY : a.bias[k];
-                const float sc = a.scale[b * a.cout + k];
+            for (int mt = 0; mt < 4; ++mt) cv[mt] = *reinterpret_cast<const float4*>(cp + 16 * mt);
+            float* op = a.out_f + row_off(b, y0, x0, r0 + r);
+            if (kc < K) {
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    float4* cp = reinterpret_cast<float4*>(s_c + kl * CP + w * PTW + 16 * mt + lm);
-                    const float4 cv = *cp;
-                    const float v[4] = {cv.x, cv.y, cv.z, cv.w};
-                    float r[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float o = acc[mt][nt][i] + bias;
-                        const float d = fminf(fmaxf(fabsf(v[i] * sc) - fmaxf(o, 0.0f), 0.0f), 0.75f);
-                        const float u = fmaxf(__builtin_amdgcn_exp2f(-fabsf(o) * L2E), o > 0.0f ? 1e-30f : 0.0f);
-                        float e = 1.0f / 362880.0f;
-                        e = fmaf(e, d, 1.0f / 40320.0f);
-                        e = fmaf(e, d, 1.0f / 5040.0f);
-                        e = fmaf(e, d, 1.0f / 720.0f);
-                        e = fmaf(e, d, 1.0f / 120.0f);
-                        e = fmaf(e, d, 1.0f / 24.0f);
-                        e = fmaf(e, d, 1.0f / 6.0f);
-                        e = fmaf(e, d, 0.5f);
-                        e = fmaf(e, d, 1.0f);
-                        r[i] = (e * d >= u) ? v[i] : 0.0f;
-                    }
-                    *cp = make_float4(r[0], r[1], r[2], r[3]);
-                }
+                for (int mt = 0; mt < 4; ++mt) *reinterpret_cast<f32x4*>(op + 16 * mt) = acc[mt];
             }
-            __syncthreads();  // the pass's shrunk coefficients are in LDS
-#pragma unroll
-            for (int j = 0; j < PassRegs<CG>::NIT; ++j) {
-                const int i = (int)threadIdx.x + j * PTHREADS;
-                const int q = i % (PTW / 4), yy = (i / (PTW / 4)) % PTH, kl = i / (PTH * PTW / 4), k = c0 + kl;
-                if (i < PassRegs<CG>::TOTAL && k < a.cout)
-                    *reinterpret_cast<float4*>(a.out_f + (((size_t)b * a.cout + k) * a.N + y0 + yy) * a.M + x0 + 4 * q) =
-                        *reinterpret_cast<const float4*>(s_c + kl * CP + yy * PTW + 4 * q);
-            }
-            if (p + 1 < NP || tn < end) __syncthreads();  // the copy-out has read the buffer
         }
+        if (lp_copy && threadIdx.x < PTH * PTW / 4) *reinterpret_cast<float4*>(a.out_f + lpo) = lp;
         if (tn >= end) break;
-        hid_store<PHH>(hr, s_h, 0);  // the next tile's activations (every wave is past its products)
+        __syncthreads();  // every wavefront is past its products
         t = tn;
         b = bn;
         y0 = yn;
         x0 = xn;
-        tn = t + stride;
-        if (tn < end) tile_origin(tn, bn, yn, xn);
     }
 }
 
@@ -1217,14 +1185,12 @@ hipError_t conv_relu_t(const ConvArgs& a, int batch, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int COUTP>
+template <int NG>
 hipError_t conv_shrink_t(const ConvArgs& a, int batch, hipStream_t st) {
-    const void* fn = reinterpret_cast<const void*>(&k_conv_shrink<COUTP>);
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SLds<COUTP>::bytes);
-    if (e != hipSuccess) return e;
+    using C = SCfg<NG>;
     const int ntiles = batch * (a.N / PTH) * (a.M / PTW);
-    const int blocks = std::max(8, a.cus / 8 * 8);  // one per CU, a multiple of the 8 XCDs
-    hipLaunchKernelGGL((k_conv_shrink<COUTP>), dim3((unsigned)blocks), dim3(PTHREADS), SLds<COUTP>::bytes, st, a, ntiles);
+    const int blocks = C::BLOCKS * std::max(8, a.cus / 8 * 8);  // a multiple of the 8 XCDs
+    hipLaunchKernelGGL((k_conv_shrink<NG>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, a, ntiles);
     return hipGetLastError();
 }
 
@@ -1319,11 +1285,11 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
         }
         return hipErrorInvalidValue;
     }
-    switch (shrink_coutp(K)) {
-        case 16: return conv_shrink_t<16>(a, batch, st);
-        case 32: return conv_shrink_t<32>(a, batch, st);
-        case 48: return conv_shrink_t<48>(a, batch, st);
-        case 64: return conv_shrink_t<64>(a, batch, st);
+    switch (std::max(1, (K - 1 + 15) / 16)) {  // groups of 16 channels up to the low-pass plane
+        case 1: return conv_shrink_t<1>(a, batch, st);
+        case 2: return conv_shrink_t<2>(a, batch, st);
+        case 3: return conv_shrink_t<3>(a, batch, st);
+        case 4: return conv_shrink_t<4>(a, batch, st);
     }
     return hipErrorInvalidValue;
 }
