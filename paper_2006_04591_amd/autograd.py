@@ -50,7 +50,8 @@ class ShearletLayer(torch.nn.Module):
         if x.dim() == 4:
             if x.shape[1] != 1:
                 raise ValueError(f"expected one input channel, got {x.shape[1]}")
-            x = x[:, 0]
+            # a view whose backward is a view: indexing's fills a zero tensor and copies the gradient into it
+            x = x.squeeze(1)
         if x.dim() != 3:
             raise ValueError(f"expected (B, rows, cols) or (B, 1, rows, cols), got {tuple(x.shape)}")
         return ShearletTransform.apply(x, self.system)
