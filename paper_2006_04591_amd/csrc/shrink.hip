@@ -40,7 +40,6 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (unsigned short)(u >> 16);
 }
-__device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(((unsigned)h) << 16); }
 
 // softplus(x) = max(x, 0) + log1p(u), u = e^{-|x|} in (0, 1], from the hardware exponential and
 // logarithm (relative error ~1e-6, far inside the threshold tolerance). log1p(u) is taken as
@@ -372,8 +371,8 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
 // The first layer (coefficients -> 32 hidden channels) as a persistent kernel: one 512-thread block
 // per CU keeps the layer's weights in LDS and walks a list of 8 x 64-pixel tiles, software
 // pipelined: while the matrix cores work on tile t out of LDS, the FP32 loads of tile t + 1 are
-// in flight in registers; then tile t's bf16 outputs leave through LDS (over the staged tile) and
-// tile t + 1 is converted into the staging buffer. Only these loads and stores use the vector-memory
+// in flight in registers; then tile t's bf16 outputs leave and tile t + 1 is converted into the staging
+// buffer. Only these loads and stores use the vector-memory
 // counter, so waiting for the prefetched tile never waits for weight loads, and the stores of
 // tile t (issued after the prefetch) are not waited for. A tile reads 256-byte runs of each
 // coefficient plane (16 x 32-pixel tiles, 128-byte runs, measured 0.49 against 0.44 ms). The tiles
@@ -390,7 +389,6 @@ struct PLds {
     static constexpr int WP = 9 * CS + 8;  // bf16 per output channel of the staged weights (padded)
     static constexpr size_t in = (size_t)PHH * PHW * PIX * 2, w = (size_t)32 * WP * 2;
     static constexpr size_t bytes = in + w;
-    static_assert((size_t)PTH * PTW * 32 * 2 <= in, "the output tile fits over the staged tile");
 };
 
 // Staged rows R0 .. R0 + NR - 1 of a tile's FP32 inputs (staged row yy is image row y0 + yy - 1),
@@ -443,9 +441,11 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
     }
 }
 
-// z = bf16(c scale) of the loaded rows -> the channel-last staging buffer (16-byte runs)
+// z = bf16(c scale) of the loaded rows -> the channel-last staging buffer (16-byte runs), a ring of PHH
+// rows whose row 0 is at slot rb
 template <int CS, int NR>
-__device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned short* s, int R0) {
+__device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned short* s, int R0, int rb) {
+    auto slot = [rb](int yy) { return yy + rb < PHH ? yy + rb : yy + rb - PHH; };
     using R = CoefRegs<CS, NR>;
     constexpr int PIX = Pix<CS>::value;
     const int g = (int)threadIdx.x % R::G;
@@ -455,7 +455,7 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
         const int i = (int)threadIdx.x + j * PTHREADS;
         if (i < R::TOTAL) {
             const int q = (i / R::G) % R::QW, yy = R0 + i / (R::G * R::QW);
-            unsigned short* d = s + (yy * PHW + 1 + 4 * q) * PIX + 8 * g;
+            unsigned short* d = s + (slot(yy) * PHW + 1 + 4 * q) * PIX + 8 * g;
             const float4* w = r.v[j];
             const uint2 p0a = pack_bf16x4(w[0].x * sc[0], w[1].x * sc[1], w[2].x * sc[2], w[3].x * sc[3]);
             const uint2 p0b = pack_bf16x4(w[4].x * sc[4], w[5].x * sc[5], w[6].x * sc[6], w[7].x * sc[7]);
@@ -479,7 +479,7 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
             const float* w = r.h[j];
             const uint2 pa = pack_bf16x4(w[0] * sc[0], w[1] * sc[1], w[2] * sc[2], w[3] * sc[3]);
             const uint2 pb = pack_bf16x4(w[4] * sc[4], w[5] * sc[5], w[6] * sc[6], w[7] * sc[7]);
-            *reinterpret_cast<uint4*>(s + (yy * PHW + (side ? PHW - 1 : 0)) * PIX + 8 * g) =
+            *reinterpret_cast<uint4*>(s + (slot(yy) * PHW + (side ? PHW - 1 : 0)) * PIX + 8 * g) =
                 make_uint4(pa.x, pa.y, pb.x, pb.y);
         }
     }
@@ -543,11 +543,11 @@ __device__ __forceinline__ void xcd_chunk(int ntiles, int& first, int& end) {
 }
 
 // the bf16 of v where the bf16 of m (a saved activation, never NaN) is > 0, else 0
-__device__ __forceinline__ uint4 positive_only(uint4 v, uint4 m) {
+__device__ __forceinline__ uint2 positive_only(uint2 v, uint2 m) {
     auto f = [](unsigned x, unsigned y) {
         return x & (((int)(y << 16) > 0 ? 0xFFFFu : 0u) | ((int)y > 0xFFFF ? 0xFFFF0000u : 0u));
     };
-    return make_uint4(f(v.x, m.x), f(v.y, m.y), f(v.z, m.z), f(v.w, m.w));
+    return make_uint2(f(v.x, m.x), f(v.y, m.y));
 }
 
 // COEF_RELU: the first layer (input: the FP32 coefficient planes, normalised and rounded on staging);
@@ -556,16 +556,20 @@ __device__ __forceinline__ uint4 positive_only(uint4 v, uint4 m) {
 // first, CINP = 32); GRAD_MASK: backward data (input: gradient planes; flipped, transposed weights; the
 // output is masked by relu's derivative, mask_act > 0, as it leaves).
 // The first layer walks its block's chunk of tiles down vertical strips (tile index: rows of tiles
-// fastest, then strips of 64 columns, then images), as a sliding window: the staged tile's last two
-// rows (its bottom halo and last row) are the next tile's first two, so they move up in LDS and
-// only 8 new rows are loaded per tile (10 at the top of a strip); neighbouring chunks of an XCD run
-// down neighbouring strips together, so the halo columns hit that XCD's L2 (0.449 -> 0.406 ms).
+// fastest, then strips of 64 columns, then images), as a sliding window over a ring of staged rows: the
+// staged tile's last two rows (its bottom halo and last row) are the next tile's first two and stay where
+// they are, and only 8 new rows are loaded per tile (10 at the top of a strip); neighbouring chunks of an
+// XCD run down neighbouring strips together, so the halo columns hit that XCD's L2 (0.449 -> 0.406 ms).
 // The other layers, whose tiles are a quarter or half of the bytes, take their tiles interleaved over
-// the XCD's blocks and load all 10 rows (the sliding window's extra barrier and copy made the hidden
-// layer slower: 0.123 -> 0.138 ms).
+// the XCD's blocks and load all 10 rows.
+// The products are taken with the weights as the first operand, so that a lane ends with 4 consecutive
+// channels of one pixel: 8 bytes that go straight to memory (a wavefront's store covers 16 pixels' 32-byte
+// halves, the next one the other halves). Through LDS, from 2-byte stores, the outputs cost two more
+// barriers and most of a tile's LDS stores, and the two rows of the sliding window were moved between two
+// more: the network's inference 894 -> 881 us at 16 x 512^2 x 49, the first layer in training 0.52 -> 0.44 ms.
 // In a training step at 16 x 512^2 x 49, z and the first layer took 0.33 + 0.40 ms as a packing pass and
 // a layer of one-tile blocks, and the backward data of the last and the hidden layer 0.41 and 0.18 ms as
-// one-tile blocks; here 0.52, 0.27 and 0.14 ms.
+// one-tile blocks; here 0.44, 0.26 and 0.15 ms.
 enum ConvKind { COEF_RELU, COEF_RELU_Z, HID_RELU, GRAD_MASK };
 template <int CINP, ConvKind KIND>
 __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) void k_conv_relu(ConvArgs a, int ntiles) {
@@ -582,18 +586,18 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
             hid_load<NR, CS>(a, r, b, y0, x0, R0);
         }
     };
-    auto store8 = [&](const Regs8& r, unsigned short* s) {
+    auto store8 = [&](const Regs8& r, unsigned short* s, [[maybe_unused]] int rb) {
         if constexpr (FROM_COEF) {
-            coef_store<CS, NR>(r, s, R0);
+            coef_store<CS, NR>(r, s, R0, rb);
         } else {
             hid_store<NR, CS>(r, s, R0);
         }
     };
-    auto stage_top = [&](unsigned short* s, int b, int y0, int x0) {  // staged rows 0, 1 straight from memory
+    auto stage_top = [&](unsigned short* s, int b, int y0, int x0, [[maybe_unused]] int rb) {  // rows 0, 1 from memory
         Regs2 r2;
         if constexpr (FROM_COEF) {
             coef_load<CS, 2>(a, r2, b, y0, x0, 0);
-            coef_store<CS, 2>(r2, s, 0);
+            coef_store<CS, 2>(r2, s, 0, rb);
         } else {
             hid_load<2, CS>(a, r2, b, y0, x0, 0);
             hid_store<2, CS>(r2, s, 0);
@@ -601,10 +605,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     };
     extern __shared__ unsigned short smem[];
     unsigned short* s_in = smem;
-    unsigned short* s_out = smem;  // the output tile, over the staged tile's first rows once the products are done
     unsigned short* s_w = smem + PLds<CS>::in / 2;
-    static_assert((size_t)PTH * PTW * 32 * 2 <= (size_t)(PHH - 2) * PHW * PIX * 2,
-                  "the output tile leaves the staged tile's last two rows intact");
     const int tx = a.M / PTW, ty = a.N / PTH;
     int t, end, stride = 1;
     if constexpr (SLIDE) {
@@ -628,24 +629,21 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         const int co = i / (9 * CS / 8), r = i % (9 * CS / 8);
         *reinterpret_cast<uint4*>(s_w + co * WP + 8 * r) = reinterpret_cast<const uint4*>(a.W)[i];
     }
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), l = threadIdx.x % 64;
     const int lr = l % 16, lm = 4 * (l / 16), lk = 8 * (l / 16);
-    [[maybe_unused]] float bias[2];
+    [[maybe_unused]] f32x4 bias[2];
     if constexpr (KIND != GRAD_MASK) {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) bias[nt] = a.bias[nt * 16 + lr];
+        for (int nt = 0; nt < 2; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(a.bias + nt * 16 + lm);
     }
-    constexpr int OU = PTH * PTW * 4 / PTHREADS;  // 16-byte units of the output tile per thread
-    auto out_unit = [&](int j, int b, int y0, int x0) {
-        const int i = (int)threadIdx.x + j * PTHREADS, ch = i % 4, p = i / 4;
-        return (((size_t)b * a.N + y0 + p / PTW) * a.M + x0 + p % PTW) * 4 + ch;
-    };
+    int rb = 0;  // ring slot of staged row 0 (SLIDE)
+    auto slot = [&](int yy) { return !SLIDE || yy + rb < PHH ? yy + rb : yy + rb - PHH; };
     Regs8 r;
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
-    if constexpr (SLIDE) stage_top(s_in, b, y0, x0);
+    if constexpr (SLIDE) stage_top(s_in, b, y0, x0, rb);
     load8(r, b, y0, x0);
-    store8(r, s_in);
+    store8(r, s_in, rb);
     if (t + stride < end) {
         int bn, yn, xn;
         tile_origin(t + stride, bn, yn, xn);
@@ -660,7 +658,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
             for (int j = 0; j < PTH * PTW * ZU / PTHREADS; ++j) {
                 const int i = (int)threadIdx.x + j * PTHREADS, ch = i % ZU, p = i / ZU, px = p % PTW, py = p / PTW;
                 z[(((size_t)b * a.N + y0 + py) * a.M + x0 + px) * ZU + ch] =
-                    *reinterpret_cast<const uint4*>(s_in + ((py + 1) * PHW + px + 1) * PIX + ch * 8);
+                    *reinterpret_cast<const uint4*>(s_in + (slot(py + 1) * PHW + px + 1) * PIX + ch * 8);
             }
         }
         // wave w: tile row w, 4 m-tiles of 16 pixels
@@ -679,66 +677,47 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const bf16x8 afr = *reinterpret_cast<const bf16x8*>(
-                    s_in + ((w + dy) * PHW + 16 * mt + lr + dx) * PIX + kc * 32 + lk);
+                    s_in + (slot(w + dy) * PHW + 16 * mt + lr + dx) * PIX + kc * 32 + lk);
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr, bf[nt], acc[mt][nt], 0, 0, 0);
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[nt], afr, acc[mt][nt], 0, 0, 0);
             }
         }
-        [[maybe_unused]] uint4 mk[OU];
-        if constexpr (KIND == GRAD_MASK) {  // in flight while the outputs pass through LDS (earlier, they spill)
-#pragma unroll
-            for (int j = 0; j < OU; ++j) mk[j] = reinterpret_cast<const uint4*>(a.mask_act)[out_unit(j, b, y0, x0)];
-        }
-        __syncthreads();  // every wave is done reading the staged tile
-        // relu(acc + bias), or the gradient -> bf16 output tile [pixel][32 channels]
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const int prow = w * PTW + 16 * mt + lm;
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    s_out[(prow + i) * 32 + nt * 16 + lr] =
-                        f2bf(KIND == GRAD_MASK ? acc[mt][nt][i] : fmaxf(acc[mt][nt][i] + bias[nt], 0.0f));
-        }
-        __syncthreads();  // the output tile is written
-        uint4* out = reinterpret_cast<uint4*>(a.out_bf);
+        // relu(acc + bias), or the masked gradient: 4 channels of a pixel per lane
+        const size_t o8 = (((size_t)b * a.N + y0 + w) * a.M + x0 + lr) * 8 + l / 16;
+        uint2* out = reinterpret_cast<uint2*>(a.out_bf) + o8;
+        [[maybe_unused]] uint2 mk[4][2];
         if constexpr (KIND == GRAD_MASK) {
 #pragma unroll
-            for (int j = 0; j < OU; ++j)
-                out[out_unit(j, b, y0, x0)] =
-                    positive_only(*reinterpret_cast<const uint4*>(s_out + ((int)threadIdx.x + j * PTHREADS) * 8), mk[j]);
-        } else {
-            for (int i = (int)threadIdx.x; i < PTH * PTW * 4; i += PTHREADS) {
-                const int ch = i % 4, p = i / 4, px = p % PTW, py = p / PTW;
-                out[(((size_t)b * a.N + y0 + py) * a.M + x0 + px) * 4 + ch] =
-                    *reinterpret_cast<const uint4*>(s_out + p * 32 + ch * 8);
-            }
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) mk[mt][nt] = (reinterpret_cast<const uint2*>(a.mask_act) + o8)[mt * 128 + nt * 4];
         }
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const f32x4 v = acc[mt][nt];
+                if constexpr (KIND == GRAD_MASK) {
+                    out[mt * 128 + nt * 4] = positive_only(pack_bf16x4(v[0], v[1], v[2], v[3]), mk[mt][nt]);
+                } else {
+                    const f32x4 c = bias[nt];
+                    out[mt * 128 + nt * 4] = pack_bf16x4(fmaxf(v[0] + c[0], 0.0f), fmaxf(v[1] + c[1], 0.0f),
+                                                       fmaxf(v[2] + c[2], 0.0f), fmaxf(v[3] + c[3], 0.0f));
+                }
+            }
         if (t + stride >= end) break;
         const int tn = t + stride;
         int bn, yn, xn;
         tile_origin(tn, bn, yn, xn);
-        __syncthreads();  // the output tile is read
-        if (!SLIDE) {
-            // every tile stages all its rows (below)
-        } else if (yn != 0) {
-            // the next tile continues the strip: its first two staged rows are this one's last two
-            constexpr int U = 2 * PHW * PIX / 8;  // 16-byte units of two staged rows
-            static_assert(U > PTHREADS && U <= 3 * PTHREADS, "two staged rows are 2 or 3 units per thread");
-            const uint4* src = reinterpret_cast<const uint4*>(s_in + PTH * PHW * PIX);
-            uint4* dst = reinterpret_cast<uint4*>(s_in);
-            const int i0 = (int)threadIdx.x, i1 = i0 + PTHREADS, i2 = i0 + 2 * PTHREADS;
-            const uint4 m0 = src[i0], m1 = src[min(i1, U - 1)], m2 = src[min(i2, U - 1)];
-            __syncthreads();  // rows 8 and 9 are read before the new rows overwrite them
-            dst[i0] = m0;
-            if (i1 < U) dst[i1] = m1;
-            if (i2 < U) dst[i2] = m2;
-        } else {
-            stage_top(s_in, bn, yn, xn);  // the top of a strip: its first two rows from memory
+        __syncthreads();  // every wave is done reading the staged tile
+        if constexpr (SLIDE) {
+            // the next tile continues the strip: its first two staged rows are this one's last two; at the
+            // top of a strip they come from memory
+            rb = rb + PTH < PHH ? rb + PTH : rb + PTH - PHH;
+            if (yn == 0) stage_top(s_in, bn, yn, xn, rb);
         }
-        store8(r, s_in);  // staged rows R0 .. 9 of tile tn, loaded during this tile's products
+        store8(r, s_in, rb);  // staged rows R0 .. 9 of tile tn, loaded during this tile's products
         t = tn;
         b = bn;
         y0 = yn;
