@@ -53,9 +53,13 @@ __device__ __forceinline__ float softplusf(float x) {
     return fmaxf(x, 0.0f) + l;
 }
 
+// bf16 per staged pixel: an odd multiple of 32 bytes, which puts the 16-byte pieces that a fragment read takes
+// together (4 consecutive pixels of one piece beside 4 others of the next piece) on distinct banks. With 16
+// bytes of padding instead of 32, an LDS instruction lost 4 cycles to conflicts: the hidden layer 115 -> 108 us,
+// the backward data 254 -> 249 and 148 -> 144, the first layer 397 -> 395 (16 x 512^2 x 49).
 template <int CINP>
 struct Pix {
-    static constexpr int value = CINP + 8;  // bf16 per staged pixel: 16 bytes of padding against bank conflicts
+    static constexpr int value = CINP + 16;
 };
 
 // LDS of a conv block: the staged input tile; the padded gradient planes of the last layer's training
@@ -386,7 +390,10 @@ constexpr int PTHREADS = 512;             // 8 wavefronts, one tile row each
 template <int CS>
 struct PLds {
     static constexpr int PIX = Pix<CS>::value;
-    static constexpr int WP = 9 * CS + 8;  // bf16 per output channel of the staged weights (padded)
+    // bf16 per output channel of the staged weights: padded like a pixel, or, at 32 channels, where two blocks
+    // have to share a CU's LDS, without padding and with the 16-byte pieces of every other group of 4
+    // output channels exchanged in pairs (WSW), which avoids the same conflicts
+    static constexpr int WP = CS == 32 ? 9 * CS : 9 * CS + 16, WSW = CS == 32 ? 16 : 0;
     static constexpr size_t in = (size_t)PHH * PHW * PIX * 2, w = (size_t)32 * WP * 2;
     static constexpr size_t bytes = in + w;
 };
@@ -510,10 +517,9 @@ __device__ __forceinline__ void hid_load(const ConvArgs& a, HidRegs<NR, C, THR>&
     }
 }
 
-template <int NR, int C = 32, int THR = PTHREADS>
+template <int NR, int C = 32, int THR = PTHREADS, int PIX = Pix<C>::value>
 __device__ __forceinline__ void hid_store(const HidRegs<NR, C, THR>& r, unsigned short* s, int R0) {
     using R = HidRegs<NR, C, THR>;
-    constexpr int PIX = Pix<C>::value;
 #pragma unroll
     for (int j = 0; j < R::NIT; ++j) {
         const int i = (int)threadIdx.x + j * THR;
@@ -625,12 +631,14 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         b = tile / (tx * ty);
     };
     // weights [co][tap][ci] -> LDS rows of WP bf16 (16-byte pieces)
+    auto swap_of = [](int co) { return co & 4 ? PLds<CS>::WSW : 0; };
     for (int i = (int)threadIdx.x; i < 32 * 9 * CS / 8; i += PTHREADS) {
         const int co = i / (9 * CS / 8), r = i % (9 * CS / 8);
-        *reinterpret_cast<uint4*>(s_w + co * WP + 8 * r) = reinterpret_cast<const uint4*>(a.W)[i];
+        *reinterpret_cast<uint4*>(s_w + co * WP + ((8 * r) ^ swap_of(co))) = reinterpret_cast<const uint4*>(a.W)[i];
     }
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), l = threadIdx.x % 64;
     const int lr = l % 16, lm = 4 * (l / 16), lk = 8 * (l / 16);
+    const int lw = lk ^ swap_of(lr);
     [[maybe_unused]] f32x4 bias[2];
     if constexpr (KIND != GRAD_MASK) {
 #pragma unroll
@@ -673,7 +681,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
             bf16x8 bf[2];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt)
-                bf[nt] = *reinterpret_cast<const bf16x8*>(s_w + (nt * 16 + lr) * WP + tap * CS + kc * 32 + lk);
+                bf[nt] = *reinterpret_cast<const bf16x8*>(s_w + (nt * 16 + lr) * WP + tap * CS + kc * 32 + lw);
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const bf16x8 afr = *reinterpret_cast<const bf16x8*>(
@@ -775,7 +783,10 @@ struct SCfg {
     static constexpr int RH = NG == 3 ? 2 : 4 / NG;  // parts of the tile's rows
     static constexpr int ROWS = PTH / RH, WAVES = NG * RH, THREADS = 64 * WAVES;
     static constexpr int BLOCKS = 12 / WAVES;  // per CU: 12 wavefronts of up to 168 registers
-    static constexpr int PIX = Pix<32>::value;
+    // three blocks fit in a CU's LDS with 80-byte pixels (96 bytes leave two: the network's
+    // inference 487 -> 557 us at 16 x 512^2 x 17); with three groups, two blocks by their registers, the wider
+    // pitch takes 873 us against 881 (16 x 512^2 x 49)
+    static constexpr int PIX = BLOCKS > 2 ? 40 : Pix<32>::value;
     static constexpr size_t LDS = (size_t)PHH * PHW * PIX * 2;
 };
 
@@ -815,7 +826,7 @@ __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) cv[mt] = *reinterpret_cast<const float4*>(a.coef + row_off(b, y0, x0, r0) + 16 * mt);
     for (;;) {
-        hid_store<PHH, 32, THR>(hr, smem, 0);
+        hid_store<PHH, 32, THR, PIX>(hr, smem, 0);
         const float sc = a.scale[b * K + k];
         const int tn = t + stride;
         int bn = b, yn = y0, xn = x0;
@@ -1156,8 +1167,8 @@ hipError_t conv_relu_t(const ConvArgs& a, int batch, hipStream_t st) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PLds<CINP>::bytes);
     if (e != hipSuccess) return e;
     const int ntiles = batch * (a.N / PTH) * (a.M / PTW);
-    // blocks per CU its registers and LDS allow (64 channels or coefficients: one, 132 KB; 32 bf16
-    // channels: two, 72 KB), a multiple of the 8 XCDs
+    // blocks per CU its registers and LDS allow (64 channels or coefficients: one, 144 KB; 32 bf16
+    // channels: two, 82 KB), a multiple of the 8 XCDs
     const int blocks = (CINP == 32 && KIND >= HID_RELU ? 2 : 1) * std::max(8, a.cus / 8 * 8);
     hipLaunchKernelGGL((k_conv_relu<CINP, KIND>), dim3((unsigned)blocks), dim3(PTHREADS), PLds<CINP>::bytes, st, a,
                        ntiles);
