@@ -373,28 +373,34 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
 
 // ---------------------------------------------------------------- persistent first layer
 // The first layer (coefficients -> 32 hidden channels) as a persistent kernel: one 512-thread block
-// per CU keeps the layer's weights in LDS and walks a list of 8 x 64-pixel tiles, software
+// per CU keeps the layer's weights in LDS and walks a list of 4 x 128-pixel tiles, software
 // pipelined: while the matrix cores work on tile t out of LDS, the FP32 loads of tile t + 1 are
 // in flight in registers; then tile t's bf16 outputs leave and tile t + 1 is converted into the staging
 // buffer. Only these loads and stores use the vector-memory
 // counter, so waiting for the prefetched tile never waits for weight loads, and the stores of
-// tile t (issued after the prefetch) are not waited for. A tile reads 256-byte runs of each
-// coefficient plane (16 x 32-pixel tiles, 128-byte runs, measured 0.49 against 0.44 ms). The tiles
+// tile t (issued after the prefetch) are not waited for. A tile reads 512-byte runs of each
+// coefficient plane. The tiles
 // of the batch are cut into 8 contiguous ranges, one per XCD (block w runs on XCD w mod 8), so
 // that the halo re-reads of neighbouring tiles hit that XCD's L2. The hidden layer (32 bf16
-// channels in, 32 out) runs in the same kernel with its own staging.
+// channels in, 32 out) runs in the same kernel with its own staging and 8 x 64-pixel tiles.
 constexpr int PTH = 8, PHH = PTH + 2;     // tile rows, with halo
 constexpr int PTW = 64, PHW = PTW + 2;    // tile columns, with halo
-constexpr int PTHREADS = 512;             // 8 wavefronts, one tile row each
+constexpr int PTHREADS = 512;             // 8 wavefronts, 64 pixels of a tile row each
+// the first layer's tiles: of its 200-byte pixels (49 planes), a tile's halo columns touch two more lines of every
+// row of a plane, beside 4 lines of 128 pixels or 2 of 64, so its tiles are half as high and twice as wide:
+// inference 878 -> 837 us at 16 x 512^2 x 49, 731 -> 706 at 33 planes; two tiles per block and less
+// (4 x 256^2 x 33), where the strip's first two rows weigh more, 55.3 -> 56.2 us
+constexpr int CTH = 4, CHH = CTH + 2, CTW = 128, CHW = CTW + 2;
 
-template <int CS>
+template <int CS, bool COEF>
 struct PLds {
+    static constexpr int TH = COEF ? CTH : PTH, TW = COEF ? CTW : PTW, HH = TH + 2, HW = TW + 2;
     static constexpr int PIX = Pix<CS>::value;
     // bf16 per output channel of the staged weights: padded like a pixel, or, at 32 channels, where two blocks
     // have to share a CU's LDS, without padding and with the 16-byte pieces of every other group of 4
     // output channels exchanged in pairs (WSW), which avoids the same conflicts
     static constexpr int WP = CS == 32 ? 9 * CS : 9 * CS + 16, WSW = CS == 32 ? 16 : 0;
-    static constexpr size_t in = (size_t)PHH * PHW * PIX * 2, w = (size_t)32 * WP * 2;
+    static constexpr size_t in = (size_t)HH * HW * PIX * 2, w = (size_t)32 * WP * 2;
     static constexpr size_t bytes = in + w;
 };
 
@@ -402,7 +408,7 @@ struct PLds {
 // held in registers between their loads and their conversion to LDS.
 template <int CS, int NR>
 struct CoefRegs {
-    static constexpr int G = CS / 8, QW = PTW / 4;
+    static constexpr int G = CS / 8, QW = CTW / 4;
     static constexpr int TOTAL = G * QW * NR, NIT = (TOTAL + PTHREADS - 1) / PTHREADS;
     static constexpr int HTOTAL = G * NR * 2, HNIT = (HTOTAL + PTHREADS - 1) / PTHREADS;
     float4 v[NIT][8];
@@ -429,7 +435,7 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
     for (int j = 0; j < R::HNIT; ++j) {
         const int i = (int)threadIdx.x + j * PTHREADS;
         const int side = (i / R::G) % 2, yy = R0 + i / (2 * R::G);
-        const int y = (y0 + yy - 1 + N) & (N - 1), x = side ? (x0 + PTW) & (M - 1) : (x0 - 1 + M) & (M - 1);
+        const int y = (y0 + yy - 1 + N) & (N - 1), x = side ? (x0 + CTW) & (M - 1) : (x0 - 1 + M) & (M - 1);
 #pragma unroll
         for (int c = 0; c < 8; ++c)
             r.h[j][c] = (i < R::HTOTAL && k0 + c < K) ? base[c * plane + (size_t)y * M + x] : 0.0f;
@@ -448,11 +454,11 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
     }
 }
 
-// z = bf16(c scale) of the loaded rows -> the channel-last staging buffer (16-byte runs), a ring of PHH
+// z = bf16(c scale) of the loaded rows -> the channel-last staging buffer (16-byte runs), a ring of CHH
 // rows whose row 0 is at slot rb
 template <int CS, int NR>
 __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned short* s, int R0, int rb) {
-    auto slot = [rb](int yy) { return yy + rb < PHH ? yy + rb : yy + rb - PHH; };
+    auto slot = [rb](int yy) { return yy + rb < CHH ? yy + rb : yy + rb - CHH; };
     using R = CoefRegs<CS, NR>;
     constexpr int PIX = Pix<CS>::value;
     const int g = (int)threadIdx.x % R::G;
@@ -462,7 +468,7 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
         const int i = (int)threadIdx.x + j * PTHREADS;
         if (i < R::TOTAL) {
             const int q = (i / R::G) % R::QW, yy = R0 + i / (R::G * R::QW);
-            unsigned short* d = s + (slot(yy) * PHW + 1 + 4 * q) * PIX + 8 * g;
+            unsigned short* d = s + (slot(yy) * CHW + 1 + 4 * q) * PIX + 8 * g;
             const float4* w = r.v[j];
             const uint2 p0a = pack_bf16x4(w[0].x * sc[0], w[1].x * sc[1], w[2].x * sc[2], w[3].x * sc[3]);
             const uint2 p0b = pack_bf16x4(w[4].x * sc[4], w[5].x * sc[5], w[6].x * sc[6], w[7].x * sc[7]);
@@ -486,7 +492,7 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
             const float* w = r.h[j];
             const uint2 pa = pack_bf16x4(w[0] * sc[0], w[1] * sc[1], w[2] * sc[2], w[3] * sc[3]);
             const uint2 pb = pack_bf16x4(w[4] * sc[4], w[5] * sc[5], w[6] * sc[6], w[7] * sc[7]);
-            *reinterpret_cast<uint4*>(s + (slot(yy) * PHW + (side ? PHW - 1 : 0)) * PIX + 8 * g) =
+            *reinterpret_cast<uint4*>(s + (slot(yy) * CHW + (side ? CHW - 1 : 0)) * PIX + 8 * g) =
                 make_uint4(pa.x, pa.y, pb.x, pb.y);
         }
     }
@@ -562,9 +568,9 @@ __device__ __forceinline__ uint2 positive_only(uint2 v, uint2 m) {
 // first, CINP = 32); GRAD_MASK: backward data (input: gradient planes; flipped, transposed weights; the
 // output is masked by relu's derivative, mask_act > 0, as it leaves).
 // The first layer walks its block's chunk of tiles down vertical strips (tile index: rows of tiles
-// fastest, then strips of 64 columns, then images), as a sliding window over a ring of staged rows: the
+// fastest, then strips of 128 columns, then images), as a sliding window over a ring of staged rows: the
 // staged tile's last two rows (its bottom halo and last row) are the next tile's first two and stay where
-// they are, and only 8 new rows are loaded per tile (10 at the top of a strip); neighbouring chunks of an
+// they are, and only 4 new rows are loaded per tile (6 at the top of a strip); neighbouring chunks of an
 // XCD run down neighbouring strips together, so the halo columns hit that XCD's L2 (0.449 -> 0.406 ms).
 // The other layers, whose tiles are a quarter or half of the bytes, take their tiles interleaved over
 // the XCD's blocks and load all 10 rows.
@@ -580,9 +586,11 @@ enum ConvKind { COEF_RELU, COEF_RELU_Z, HID_RELU, GRAD_MASK };
 template <int CINP, ConvKind KIND>
 __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) void k_conv_relu(ConvArgs a, int ntiles) {
     constexpr bool FROM_COEF = KIND == COEF_RELU || KIND == COEF_RELU_Z;
-    constexpr int CS = CINP, PIX = Pix<CS>::value, WP = PLds<CS>::WP, KCN = CS / 32, STEPS = 9 * KCN;
+    constexpr int CS = CINP, PIX = Pix<CS>::value, WP = PLds<CS, FROM_COEF>::WP, KCN = CS / 32, STEPS = 9 * KCN;
     constexpr bool SLIDE = FROM_COEF;
-    constexpr int R0 = SLIDE ? 2 : 0, NR = PHH - R0;  // staged rows loaded per tile (the prefetch)
+    using L = PLds<CS, FROM_COEF>;
+    constexpr int TH = L::TH, TW = L::TW, HH = L::HH, HW = L::HW;
+    constexpr int R0 = SLIDE ? 2 : 0, NR = HH - R0;  // staged rows loaded per tile (the prefetch)
     using Regs8 = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR, CS>>::type;
     using Regs2 = typename std::conditional<FROM_COEF, CoefRegs<CS, 2>, HidRegs<2, CS>>::type;
     auto load8 = [&](Regs8& r, int b, int y0, int x0) {  // staged rows R0 .. 9
@@ -611,8 +619,8 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     };
     extern __shared__ unsigned short smem[];
     unsigned short* s_in = smem;
-    unsigned short* s_w = smem + PLds<CS>::in / 2;
-    const int tx = a.M / PTW, ty = a.N / PTH;
+    unsigned short* s_w = smem + PLds<CS, FROM_COEF>::in / 2;
+    const int tx = a.M / TW, ty = a.N / TH;
     int t, end, stride = 1;
     if constexpr (SLIDE) {
         xcd_chunk(ntiles, t, end);
@@ -622,22 +630,23 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     if (t >= end) return;  // the whole block: no tile
     auto tile_origin = [&](int tile, int& b, int& y0, int& x0) {
         if constexpr (SLIDE) {
-            y0 = (tile % ty) * PTH;
-            x0 = ((tile / ty) % tx) * PTW;
+            y0 = (tile % ty) * TH;
+            x0 = ((tile / ty) % tx) * TW;
         } else {
-            x0 = (tile % tx) * PTW;
-            y0 = ((tile / tx) % ty) * PTH;
+            x0 = (tile % tx) * TW;
+            y0 = ((tile / tx) % ty) * TH;
         }
         b = tile / (tx * ty);
     };
     // weights [co][tap][ci] -> LDS rows of WP bf16 (16-byte pieces)
-    auto swap_of = [](int co) { return co & 4 ? PLds<CS>::WSW : 0; };
+    auto swap_of = [](int co) { return co & 4 ? PLds<CS, FROM_COEF>::WSW : 0; };
     for (int i = (int)threadIdx.x; i < 32 * 9 * CS / 8; i += PTHREADS) {
         const int co = i / (9 * CS / 8), r = i % (9 * CS / 8);
         *reinterpret_cast<uint4*>(s_w + co * WP + ((8 * r) ^ swap_of(co))) = reinterpret_cast<const uint4*>(a.W)[i];
     }
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), l = threadIdx.x % 64;
     const int lr = l % 16, lm = 4 * (l / 16), lk = 8 * (l / 16);
+    const int wr = w / (TW / 64), wc = 64 * (w % (TW / 64));  // the wavefront's pixels in the tile
     const int lw = lk ^ swap_of(lr);
     [[maybe_unused]] f32x4 bias[2];
     if constexpr (KIND != GRAD_MASK) {
@@ -645,7 +654,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         for (int nt = 0; nt < 2; ++nt) bias[nt] = *reinterpret_cast<const f32x4*>(a.bias + nt * 16 + lm);
     }
     int rb = 0;  // ring slot of staged row 0 (SLIDE)
-    auto slot = [&](int yy) { return !SLIDE || yy + rb < PHH ? yy + rb : yy + rb - PHH; };
+    auto slot = [&](int yy) { return !SLIDE || yy + rb < HH ? yy + rb : yy + rb - HH; };
     Regs8 r;
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
@@ -663,10 +672,10 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
             constexpr int ZU = CS / 8;
             uint4* z = reinterpret_cast<uint4*>(a.z);
 #pragma unroll
-            for (int j = 0; j < PTH * PTW * ZU / PTHREADS; ++j) {
-                const int i = (int)threadIdx.x + j * PTHREADS, ch = i % ZU, p = i / ZU, px = p % PTW, py = p / PTW;
+            for (int j = 0; j < TH * TW * ZU / PTHREADS; ++j) {
+                const int i = (int)threadIdx.x + j * PTHREADS, ch = i % ZU, p = i / ZU, px = p % TW, py = p / TW;
                 z[(((size_t)b * a.N + y0 + py) * a.M + x0 + px) * ZU + ch] =
-                    *reinterpret_cast<const uint4*>(s_in + (slot(py + 1) * PHW + px + 1) * PIX + ch * 8);
+                    *reinterpret_cast<const uint4*>(s_in + (slot(py + 1) * HW + px + 1) * PIX + ch * 8);
             }
         }
         // wave w: tile row w, 4 m-tiles of 16 pixels
@@ -685,14 +694,14 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const bf16x8 afr = *reinterpret_cast<const bf16x8*>(
-                    s_in + (slot(w + dy) * PHW + 16 * mt + lr + dx) * PIX + kc * 32 + lk);
+                    s_in + (slot(wr + dy) * HW + wc + 16 * mt + lr + dx) * PIX + kc * 32 + lk);
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
                     acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[nt], afr, acc[mt][nt], 0, 0, 0);
             }
         }
         // relu(acc + bias), or the masked gradient: 4 channels of a pixel per lane
-        const size_t o8 = (((size_t)b * a.N + y0 + w) * a.M + x0 + lr) * 8 + l / 16;
+        const size_t o8 = (((size_t)b * a.N + y0 + wr) * a.M + x0 + wc + lr) * 8 + l / 16;
         uint2* out = reinterpret_cast<uint2*>(a.out_bf) + o8;
         [[maybe_unused]] uint2 mk[4][2];
         if constexpr (KIND == GRAD_MASK) {
@@ -722,7 +731,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         if constexpr (SLIDE) {
             // the next tile continues the strip: its first two staged rows are this one's last two; at the
             // top of a strip they come from memory
-            rb = rb + PTH < PHH ? rb + PTH : rb + PTH - PHH;
+            rb = rb + TH < HH ? rb + TH : rb + TH - HH;
             if (yn == 0) stage_top(s_in, bn, yn, xn, rb);
         }
         store8(r, s_in, rb);  // staged rows R0 .. 9 of tile tn, loaded during this tile's products
@@ -1163,14 +1172,15 @@ hipError_t conv_t(const ConvArgs& a, int batch, hipStream_t st) {
 
 template <int CINP, ConvKind KIND>
 hipError_t conv_relu_t(const ConvArgs& a, int batch, hipStream_t st) {
+    using L = PLds<CINP, (KIND < HID_RELU)>;
     const void* fn = reinterpret_cast<const void*>(&k_conv_relu<CINP, KIND>);
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PLds<CINP>::bytes);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L::bytes);
     if (e != hipSuccess) return e;
-    const int ntiles = batch * (a.N / PTH) * (a.M / PTW);
-    // blocks per CU its registers and LDS allow (64 channels or coefficients: one, 144 KB; 32 bf16
+    const int ntiles = batch * (a.N / L::TH) * (a.M / L::TW);
+    // blocks per CU its registers and LDS allow (64 channels or coefficients: one, 159 KB; 32 bf16
     // channels: two, 82 KB), a multiple of the 8 XCDs
     const int blocks = (CINP == 32 && KIND >= HID_RELU ? 2 : 1) * std::max(8, a.cus / 8 * 8);
-    hipLaunchKernelGGL((k_conv_relu<CINP, KIND>), dim3((unsigned)blocks), dim3(PTHREADS), PLds<CINP>::bytes, st, a,
+    hipLaunchKernelGGL((k_conv_relu<CINP, KIND>), dim3((unsigned)blocks), dim3(PTHREADS), L::bytes, st, a,
                        ntiles);
     return hipGetLastError();
 }
