@@ -386,10 +386,10 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
 constexpr int PTH = 8, PHH = PTH + 2;     // tile rows, with halo
 constexpr int PTW = 64, PHW = PTW + 2;    // tile columns, with halo
 constexpr int PTHREADS = 512;             // 8 wavefronts, 64 pixels of a tile row each
-// the first layer's tiles: of its 200-byte pixels (49 planes), a tile's halo columns touch two more lines of every
+// the first layer's tiles: its input is FP32 planes, and a tile's halo columns touch two more lines of every
 // row of a plane, beside 4 lines of 128 pixels or 2 of 64, so its tiles are half as high and twice as wide:
 // inference 878 -> 837 us at 16 x 512^2 x 49, 731 -> 706 at 33 planes; two tiles per block and less
-// (4 x 256^2 x 33), where the strip's first two rows weigh more, 55.3 -> 56.2 us
+// (4 x 256^2 x 33), where a strip's first two rows weigh more, 55.3 -> 56.2 us
 constexpr int CTH = 4, CHH = CTH + 2, CTW = 128, CHW = CTW + 2;
 
 template <int CS, bool COEF>
@@ -413,16 +413,15 @@ struct CoefRegs {
     static constexpr int HTOTAL = G * NR * 2, HNIT = (HTOTAL + PTHREADS - 1) / PTHREADS;
     float4 v[NIT][8];
     float h[HNIT][8];
-    float sc[8];
 };
 
 // Loads staged rows R0 .. R0 + NR - 1 of tile (b, y0, x0) in units of 8 consecutive channels (one
 // 16-byte run of a staged pixel) of 4 consecutive interior pixels of one row: 8 aligned 16-byte
 // loads, one per channel plane. Lanes take the channel groups fastest: in each load instruction the
 // lanes of one group read consecutive 16-byte pieces of a row of a plane. A lane's channel group is
-// fixed (512 is a multiple of G), and so are its 8 scales within a tile. The two halo columns come
-// one value per channel.
-template <int CS, int NR>
+// fixed (512 is a multiple of G), and so are its 8 scales within an image. The two halo columns come
+// one value per channel. J: only unit J of the interior, or, with J = NIT, only the halo.
+template <int CS, int NR, int J = -1>
 __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r, int b, int y0, int x0, int R0) {
     using R = CoefRegs<CS, NR>;
     const int N = a.N, M = a.M, K = a.cin;
@@ -430,9 +429,8 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
     const size_t plane = (size_t)N * M;
     const float* base = a.coef + ((size_t)b * K + k0) * plane;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) r.sc[c] = (k0 + c < K) ? a.scale[b * K + k0 + c] : 0.0f;
-#pragma unroll
     for (int j = 0; j < R::HNIT; ++j) {
+        if (J >= 0 && J != R::NIT) break;
         const int i = (int)threadIdx.x + j * PTHREADS;
         const int side = (i / R::G) % 2, yy = R0 + i / (2 * R::G);
         const int y = (y0 + yy - 1 + N) & (N - 1), x = side ? (x0 + CTW) & (M - 1) : (x0 - 1 + M) & (M - 1);
@@ -442,6 +440,7 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
     }
 #pragma unroll
     for (int j = 0; j < R::NIT; ++j) {
+        if (J >= 0 && J != j) continue;
         const int i = (int)threadIdx.x + j * PTHREADS;
         const int q = (i / R::G) % R::QW, yy = R0 + i / (R::G * R::QW);
         const int y = (y0 + yy - 1 + N) & (N - 1);
@@ -456,15 +455,15 @@ __device__ __forceinline__ void coef_load(const ConvArgs& a, CoefRegs<CS, NR>& r
 
 // z = bf16(c scale) of the loaded rows -> the channel-last staging buffer (16-byte runs), a ring of CHH
 // rows whose row 0 is at slot rb
-template <int CS, int NR>
-__device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned short* s, int R0, int rb) {
+template <int CS, int NR, int J = -1>
+__device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, const float* sc, unsigned short* s, int R0, int rb) {
     auto slot = [rb](int yy) { return yy + rb < CHH ? yy + rb : yy + rb - CHH; };
     using R = CoefRegs<CS, NR>;
     constexpr int PIX = Pix<CS>::value;
     const int g = (int)threadIdx.x % R::G;
-    const float* sc = r.sc;
 #pragma unroll
     for (int j = 0; j < R::NIT; ++j) {
+        if (J >= 0 && J != j) continue;
         const int i = (int)threadIdx.x + j * PTHREADS;
         if (i < R::TOTAL) {
             const int q = (i / R::G) % R::QW, yy = R0 + i / (R::G * R::QW);
@@ -486,6 +485,7 @@ __device__ __forceinline__ void coef_store(const CoefRegs<CS, NR>& r, unsigned s
     }
 #pragma unroll
     for (int j = 0; j < R::HNIT; ++j) {
+        if (J >= 0 && J != R::NIT) break;
         const int i = (int)threadIdx.x + j * PTHREADS;
         if (i < R::HTOTAL) {
             const int side = (i / R::G) % 2, yy = R0 + i / (2 * R::G);
@@ -593,6 +593,16 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     constexpr int R0 = SLIDE ? 2 : 0, NR = HH - R0;  // staged rows loaded per tile (the prefetch)
     using Regs8 = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR, CS>>::type;
     using Regs2 = typename std::conditional<FROM_COEF, CoefRegs<CS, 2>, HidRegs<2, CS>>::type;
+    // the scales of the lane's 8 channels, of image bsc; they are loaded where the image changes, and waited for
+    // there, so that no wait for them holds up a tile's loads
+    [[maybe_unused]] float sc[8];
+    [[maybe_unused]] auto scales = [&](int b) {
+        const int k0 = 8 * ((int)threadIdx.x % (CS / 8));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sc[c] = (k0 + c < a.cin) ? a.scale[b * a.cin + k0 + c] : 0.0f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sc[c]));
+    };
     auto load8 = [&](Regs8& r, int b, int y0, int x0) {  // staged rows R0 .. 9
         if constexpr (FROM_COEF) {
             coef_load<CS, NR>(a, r, b, y0, x0, R0);
@@ -602,7 +612,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     };
     auto store8 = [&](const Regs8& r, unsigned short* s, [[maybe_unused]] int rb) {
         if constexpr (FROM_COEF) {
-            coef_store<CS, NR>(r, s, R0, rb);
+            coef_store<CS, NR>(r, sc, s, R0, rb);
         } else {
             hid_store<NR, CS>(r, s, R0);
         }
@@ -611,7 +621,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         Regs2 r2;
         if constexpr (FROM_COEF) {
             coef_load<CS, 2>(a, r2, b, y0, x0, 0);
-            coef_store<CS, 2>(r2, s, 0, rb);
+            coef_store<CS, 2>(r2, sc, s, 0, rb);
         } else {
             hid_load<2, CS>(a, r2, b, y0, x0, 0);
             hid_store<2, CS>(r2, s, 0);
@@ -658,7 +668,10 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     Regs8 r;
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
-    if constexpr (SLIDE) stage_top(s_in, b, y0, x0, rb);
+    if constexpr (SLIDE) {
+        scales(b);
+        stage_top(s_in, b, y0, x0, rb);
+    }
     load8(r, b, y0, x0);
     store8(r, s_in, rb);
     if (t + stride < end) {
@@ -732,18 +745,33 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
             // the next tile continues the strip: its first two staged rows are this one's last two; at the
             // top of a strip they come from memory
             rb = rb + TH < HH ? rb + TH : rb + TH - HH;
+            if (bn != b) scales(bn);
             if (yn == 0) stage_top(s_in, bn, yn, xn, rb);
         }
-        store8(r, s_in, rb);  // staged rows R0 .. 9 of tile tn, loaded during this tile's products
+        // The new staged rows of tile tn, loaded during this tile's products, make way for those of the one after,
+        // piece by piece: memory is asked again while the rest is still being converted. With all conversions
+        // before all loads the network's inference took 846 us against 824 (16 x 512^2 x 49), 713 against 687 (33).
+        const bool more = tn + stride < end;
+        int bq, yq, xq;
+        tile_origin(more ? tn + stride : tn, bq, yq, xq);
+        if constexpr (SLIDE) {
+            constexpr int NIT = Regs8::NIT;
+            coef_store<CS, NR, NIT>(r, sc, s_in, R0, rb);
+            if (more) coef_load<CS, NR, NIT>(a, r, bq, yq, xq, R0);
+            coef_store<CS, NR, 0>(r, sc, s_in, R0, rb);
+            if (more) coef_load<CS, NR, 0>(a, r, bq, yq, xq, R0);
+            if constexpr (NIT == 2) {
+                coef_store<CS, NR, 1>(r, sc, s_in, R0, rb);
+                if (more) coef_load<CS, NR, 1>(a, r, bq, yq, xq, R0);
+            }
+        } else {
+            store8(r, s_in, rb);
+            if (more) load8(r, bq, yq, xq);
+        }
         t = tn;
         b = bn;
         y0 = yn;
         x0 = xn;
-        if (t + stride < end) {
-            int bq, yq, xq;
-            tile_origin(t + stride, bq, yq, xq);
-            load8(r, bq, yq, xq);
-        }
         __syncthreads();  // the next tile is staged
     }
 }
