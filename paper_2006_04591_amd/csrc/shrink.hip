@@ -63,11 +63,11 @@ struct Pix {
 };
 
 // LDS of a conv block: the staged input tile; the padded gradient planes of the last layer's training
-// epilogue reuse it once the products are done. The shrink epilogue (MODE 2, 5) works from registers.
+// epilogue reuse it once the products are done. The shrink epilogue (MODE 5) works from registers.
 template <int CINP, int OUTC, int MODE>
 constexpr size_t conv_lds_bytes() {
     constexpr size_t in = (size_t)HH * HW * Pix<CINP>::value * 2, out = (size_t)TH * TW * OUTC * 2;
-    return (MODE == 2 || MODE == 5 || in >= out) ? in : out;
+    return (MODE == 5 || in >= out) ? in : out;
 }
 
 // The training loss of one coefficient, with o the network's output and z, zc the noisy and clean
@@ -213,8 +213,7 @@ __device__ __forceinline__ int conv_tile() {
     return (w % 8) * per + w / 8;
 }
 
-// MODE 2: activations -> o + b -> shrink of the coefficients where |c scale| >= tau = softplus(o);
-// MODE 5: MODE 2 that also writes tau;
+// MODE 5: activations -> o + b -> shrink of the coefficients where |c scale| >= tau = softplus(o), and tau;
 // MODE 3 (training, last layer): o -> smooth-gate loss (each tile's sum to loss[tile]) and its gradient d o,
 //   stored as bf16 channel-last planes [b][y][x][OUTC] (zero beyond COUTP and on the low-pass plane).
 template <int CINP, int COUTP, int MODE, int OUTC = 32>
@@ -225,7 +224,7 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
     const int tx = a.M / TW, ty = a.N / TH, tile = conv_tile();
     const int bx = tile % tx, by = (tile / tx) % ty, b = tile / (tx * ty);
     const int x0 = bx * TW, y0 = by * TH;
-    constexpr bool SHRINK = (MODE == 2 || MODE == 5);
+    constexpr bool SHRINK = MODE == 5;
     stage<CINP>(a, s_in, b, y0, x0);
     __syncthreads();
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
@@ -236,18 +235,8 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
         // coefficient planes directly as 16-byte vectors. At most 32 output channels per pass over
         // the staged tile, so that fewer accumulators leave room for more waves per SIMD.
         // (48 padded channels go in three passes of 16: a pass never reads weight rows past COUTP)
-        // MODE 5 writes tau and decides with it. MODE 2 (no tau output) decides without forming
-        // tau: with a = |c scale| >= 0, m = max(o, 0), u = e^-|o| in (0, 1] and d = a - m,
-        // softplus(o) = m + log1p(u), so a >= softplus(o) <=> expm1(d) >= u. d is clamped to
-        // [0, 0.75] (below 0, expm1 < 0 < u; above, expm1 > 1 >= u), where expm1 is its Taylor
-        // polynomial of degree 9 (remainder < 2e-8 relative), and for o > 0, u is kept above 1e-30
-        // (beyond o = 87 it underflows: then softplus(o) = o in FP32 and the test is d > 0). The
-        // low-pass plane takes o = -inf: u = 0, every coefficient kept. One hardware exponential replaces
-        // softplus's exponential, logarithm and reciprocal, with no branch, and the decision keeps
-        // softplus's relative precision for small and large thresholds alike.
         constexpr int CG = COUTP <= 32 ? COUTP : (COUTP % 32 == 0 ? 32 : 16), NG = CG / 16;
         static_assert(COUTP % CG == 0, "the passes cover the padded output channels exactly");
-        constexpr float L2E = 1.44269504088896341f;
         // offset of the lane's first vector in a plane: row y0 + 2 w, column x0 + lm; vector mt is
         // (mt / 2) rows and (mt % 2) 16 columns further
         const size_t pix0 = (size_t)(y0 + 2 * w) * a.M + x0 + lm;
@@ -294,28 +283,11 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
                 float t[4], r[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    if constexpr (MODE == 2) {
-                        const float o = acc[mt][nt][i] + (lowpass ? -INFINITY : bias);
-                        const float d = fminf(fmaxf(fabsf(v[i] * sc) - fmaxf(o, 0.0f), 0.0f), 0.75f);
-                        const float u = fmaxf(__builtin_amdgcn_exp2f(-fabsf(o) * L2E), o > 0.0f ? 1e-30f : 0.0f);
-                        float e = 1.0f / 362880.0f;
-                        e = fmaf(e, d, 1.0f / 40320.0f);
-                        e = fmaf(e, d, 1.0f / 5040.0f);
-                        e = fmaf(e, d, 1.0f / 720.0f);
-                        e = fmaf(e, d, 1.0f / 120.0f);
-                        e = fmaf(e, d, 1.0f / 24.0f);
-                        e = fmaf(e, d, 1.0f / 6.0f);
-                        e = fmaf(e, d, 0.5f);
-                        e = fmaf(e, d, 1.0f);
-                        r[i] = (e * d >= u) ? v[i] : 0.0f;
-                    } else {
-                        t[i] = lowpass ? 0.0f : softplusf(acc[mt][nt][i] + bias);
-                        r[i] = (fabsf(v[i] * sc) >= t[i]) ? v[i] : 0.0f;
-                    }
+                    t[i] = lowpass ? 0.0f : softplusf(acc[mt][nt][i] + bias);
+                    r[i] = (fabsf(v[i] * sc) >= t[i]) ? v[i] : 0.0f;
                 }
                 *reinterpret_cast<float4*>(op + vo) = make_float4(r[0], r[1], r[2], r[3]);
-                if constexpr (MODE == 5)
-                    *reinterpret_cast<float4*>(a.tau + offs[nt] + vo) = make_float4(t[0], t[1], t[2], t[3]);
+                *reinterpret_cast<float4*>(a.tau + offs[nt] + vo) = make_float4(t[0], t[1], t[2], t[3]);
             }
         }
         }
