@@ -749,7 +749,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 }
 
 // ---------------------------------------------------------------- persistent shrink layer
-// The last layer with the shrink decision (no tau output), persistent: two or three blocks per CU walk their
+// The last layer with the shrink decision (and, TAU, the thresholds it is taken with), persistent: two or three blocks per CU walk their
 // XCD's range of 8 x 64-pixel tiles. A wavefront keeps the weights of one group of 16 output channels in
 // registers (36 VGPRs) and takes PTH / RH rows of the tile: per row, 4 m-tiles of 16 pixels x 9 taps of
 // products out of the staged activations, then the decision on the row's coefficients where the matrix
@@ -799,7 +799,7 @@ struct SCfg {
     static constexpr size_t LDS = (size_t)PHH * PHW * PIX * 2;
 };
 
-template <int NG>
+template <int NG, bool TAU>
 __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs a, int ntiles) {
     using C = SCfg<NG>;
     constexpr int PIX = C::PIX, THR = C::THREADS;
@@ -824,7 +824,8 @@ __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
         wf[tap] = *reinterpret_cast<const bf16x8*>(a.W + ((size_t)kc * 9 + tap) * 32 + lk);
-    const float bias = k == a.lowpass ? -INFINITY : a.bias[k];
+    const bool lowpass = k == a.lowpass;
+    const float bias = lowpass && !TAU ? -INFINITY : a.bias[k];
     const size_t plane = (size_t)a.N * a.M;
     auto row_off = [&](int b, int y0, int x0, int r) { return ((size_t)b * K + k) * plane + (size_t)(y0 + r) * a.M + x0 + lm; };
     H hr;
@@ -863,8 +864,17 @@ __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const float4 c = cv[mt];
-                acc[mt] = f32x4{shrink_keep(c.x, sc, acc[mt][0] + bias), shrink_keep(c.y, sc, acc[mt][1] + bias),
-                                shrink_keep(c.z, sc, acc[mt][2] + bias), shrink_keep(c.w, sc, acc[mt][3] + bias)};
+                if constexpr (TAU) {
+                    f32x4 t;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[e] = lowpass ? 0.0f : softplusf(acc[mt][e] + bias);
+                    if (kc < K) *reinterpret_cast<f32x4*>(a.tau + row_off(b, y0, x0, r0 + r) + 16 * mt) = t;
+                    acc[mt] = f32x4{fabsf(c.x * sc) >= t[0] ? c.x : 0.0f, fabsf(c.y * sc) >= t[1] ? c.y : 0.0f,
+                                    fabsf(c.z * sc) >= t[2] ? c.z : 0.0f, fabsf(c.w * sc) >= t[3] ? c.w : 0.0f};
+                } else {
+                    acc[mt] = f32x4{shrink_keep(c.x, sc, acc[mt][0] + bias), shrink_keep(c.y, sc, acc[mt][1] + bias),
+                                    shrink_keep(c.z, sc, acc[mt][2] + bias), shrink_keep(c.w, sc, acc[mt][3] + bias)};
+                }
             }
             // the next row's coefficients, of this tile or the first of the next one, in flight during its
             // products; issued before this row's stores, so that they need not wait for those
@@ -877,7 +887,10 @@ __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs
                 for (int mt = 0; mt < 4; ++mt) *reinterpret_cast<f32x4*>(op + 16 * mt) = acc[mt];
             }
         }
-        if (lp_copy && threadIdx.x < PTH * PTW / 4) *reinterpret_cast<float4*>(a.out_f + lpo) = lp;
+        if (lp_copy && threadIdx.x < PTH * PTW / 4) {
+            *reinterpret_cast<float4*>(a.out_f + lpo) = lp;
+            if constexpr (TAU) *reinterpret_cast<float4*>(a.tau + lpo) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
         if (tn >= end) break;
         __syncthreads();  // every wavefront is past its products
         t = tn;
@@ -1190,7 +1203,12 @@ hipError_t conv_shrink_t(const ConvArgs& a, int batch, hipStream_t st) {
     using C = SCfg<NG>;
     const int ntiles = batch * (a.N / PTH) * (a.M / PTW);
     const int blocks = C::BLOCKS * std::max(8, a.cus / 8 * 8);  // a multiple of the 8 XCDs
-    hipLaunchKernelGGL((k_conv_shrink<NG>), dim3((unsigned)blocks), dim3(C::THREADS), C::LDS, st, a, ntiles);
+    const dim3 g((unsigned)blocks), t(C::THREADS);
+    if (a.tau) {
+        hipLaunchKernelGGL((k_conv_shrink<NG, true>), g, t, C::LDS, st, a, ntiles);
+    } else {
+        hipLaunchKernelGGL((k_conv_shrink<NG, false>), g, t, C::LDS, st, a, ntiles);
+    }
     return hipGetLastError();
 }
 
@@ -1276,7 +1294,11 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
     }
     if (layer == 4 || (layer == 5 && c32)) return conv_relu_t<32, GRAD_MASK>(a, batch, st);  // backward data
     if (layer == 5) return conv_relu_t<64, GRAD_MASK>(a, batch, st);
-    if (a.tau) {  // the shrink layer that also writes the thresholds
+    // With the thresholds as an output: one-tile blocks of 8 x 32 pixels below half a persistent tile (8 x 64) per
+    // CU, where their number counts (128^2 x 17: 23.3 us for the network against 25.2 persistent at 32
+    // tiles, 24.8 against 25.8 at 64), the persistent kernel from there on (28.5 -> 27.7 us at 128 tiles, 16 x 512^2 x
+    // 49: 1265 -> 1114). Both sum and decide alike, bit by bit.
+    if (a.tau && 2 * batch * (a.N / PTH) * (a.M / PTW) < a.cus) {
         switch (shrink_coutp(K)) {
             case 16: return conv_t<32, 16, 5>(a, batch, st);
             case 32: return conv_t<32, 32, 5>(a, batch, st);
