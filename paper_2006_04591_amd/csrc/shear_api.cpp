@@ -9,6 +9,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <limits>
 #include <new>
 #include <string>
 #include <vector>
@@ -1258,11 +1259,15 @@ int shear_shrink_train_step(shear_system* s, const float* c_noisy, const float* 
     a.out_bf = dO;
     a.coef2 = c_clean;
     a.loss = (float*)(w + o_lp);
-    a.loss_scale = (float)(1.0 / ((double)batch * (K - 1 > 0 ? K - 1 : 1) * N * M));
-    a.temperature = temperature;
+    const float loss_scale = (float)(1.0 / ((double)batch * (K - 1 > 0 ? K - 1 : 1) * N * M));
+    // log2(e) / temperature as a float and the rest (a temperature below 4e-39 would overflow it)
+    const double gate_e = std::min(1.4426950408889634074 / (double)temperature, (double)std::numeric_limits<float>::max());
+    a.gate_ehi = (float)gate_e;
+    a.gate_elo = (float)(gate_e - (double)a.gate_ehi);
+    a.gate_c = (float)(-2.0 * (double)loss_scale / (double)temperature);
     a.cout = K;
     if ((e = shear::launch_conv(3, K, a, batch, st)) != hipSuccess) return hip_fail(e, "layer 3 (loss)");
-    if ((e = shear::launch_loss_sum(a.loss, ntiles, a.loss_scale, loss, st)) != hipSuccess) return hip_fail(e, "loss sum");
+    if ((e = shear::launch_loss_sum(a.loss, ntiles, loss_scale, loss, st)) != hipSuccess) return hip_fail(e, "loss sum");
     // backward: dW3, dh2, dW2, dh1, dW1
     shear::WgradArgs g{};
     g.batch = batch;

@@ -30,7 +30,7 @@ struct ConvArgs {
     const float* coef2;                // layer 2 training: coefficients of the clean images
     const unsigned short* mask_act;    // backward data: saved activation whose relu mask applies
     float* loss;                       // layer 2 training: each 8 x 32 tile's sum of squared residuals
-    float loss_scale, temperature;
+    float gate_ehi, gate_elo, gate_c;  // log2(e) / temperature in two parts, -2 loss scale / temperature
     int cus;  // compute units of the device (grid of the persistent layers)
 };
 

@@ -41,17 +41,17 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     return (unsigned short)(u >> 16);
 }
 
-// softplus(x) = max(x, 0) + log1p(u), u = e^{-|x|} in (0, 1], from the hardware exponential and
-// logarithm (relative error ~1e-6, far inside the threshold tolerance). log1p(u) is taken as
+// softplus(x) = max(x, 0) + log1p(u), u = e^{-|x|} in (0, 1], with the hardware logarithm (and, in softplusf,
+// the hardware exponential: relative error ~1e-6, far inside the threshold tolerance). log1p(u) is taken as
 // log(w) u / (w - 1) with w = 1 + u rounded, which cancels the rounding of w (Goldberg, 1991,
 // "What every computer scientist should know about floating-point arithmetic", Theorem 4);
 // when w rounds to 1, log1p(u) = u to working precision.
-__device__ __forceinline__ float softplusf(float x) {
-    const float u = __expf(-fabsf(x));
+__device__ __forceinline__ float softplus_of(float x, float u) {
     const float w = 1.0f + u;
     const float l = (w == 1.0f) ? u : __logf(w) * (u * __builtin_amdgcn_rcpf(w - 1.0f));
     return fmaxf(x, 0.0f) + l;
 }
+__device__ __forceinline__ float softplusf(float x) { return softplus_of(x, __expf(-fabsf(x))); }
 
 // bf16 per staged pixel: an odd multiple of 32 bytes, which puts the 16-byte pieces that a fragment read takes
 // together (4 consecutive pixels of one piece beside 4 others of the next piece) on distinct banks. With 16
@@ -70,27 +70,47 @@ constexpr size_t conv_lds_bytes() {
     return (MODE == 5 || in >= out) ? in : out;
 }
 
+// 2^(x c) for c given as the float chi and the rest clo, to about an ulp: the rounding error of x chi and the
+// product x clo enter as a factor 1 + ln 2 times their sum (a rounded product alone would cost |x c| / 2 ulp
+// of the result, the rounding of c as much again). Beyond 2^126 it stays there, so that 1 + 2^(x c) has a normal
+// reciprocal; NaN stays NaN.
+__device__ __forceinline__ float exp2_product(float x, float chi, float clo) {
+    constexpr float LN2 = 0.693147180559945309f;
+    const float t = x * chi;
+    const float e = __builtin_amdgcn_exp2f(t > 126.0f ? 126.0f : t);
+    const float lo = fabsf(t) < 126.0f ? fmaf(x, clo, fmaf(x, chi, -t)) : 0.0f;
+    return fmaf(e, lo * LN2, e);
+}
+// 1 / w, 1 <= w <= 2^126 + 1: the hardware's reciprocal and one Newton step
+__device__ __forceinline__ float rcp_newton(float w) {
+    const float r = __builtin_amdgcn_rcpf(w);
+    return fmaf(fmaf(-w, r, 1.0f), r, r);
+}
+
 // The training loss of one coefficient, with o the network's output and z, zc the noisy and clean
 // coefficients in noise units: tau = softplus(o), g = sigmoid((|z| - tau) / T), r = z g - zc; adds r^2 to
 // lsum and gives v = d(loss_scale r^2) / d o = -2 loss_scale / T r z g (1 - g) sigmoid(o). With
-// u = e^-|o| and w = 1 + u, softplus(o) = max(o, 0) + log w (here the absolute error, that of log w, is
-// what counts: it enters |z| - tau) and sigmoid(o) is 1 / w or u / w, so the three functions of o share
-// one exponential and one reciprocal, and all come from the hardware's. The library's expf, IEEE
-// divisions and a separate sigmoid took about three times the instructions, and the epilogue, 205 M
-// values at 16 x 512^2 x 49, is bound by them: layer 0.99 -> 0.60 ms (with the low-pass group left out).
+// u = e^-|o| and w = 1 + u, softplus(o) comes from u and sigmoid(o) is 1 / w or u / w, so the three functions of
+// o share one exponential; the division by T is part of the gate's exponent. tau keeps softplus's
+// relative precision for small thresholds too (log w alone loses it: below o = -17 it is 0, and a small
+// temperature magnifies the loss before that). The exponentials are within about an ulp and the
+// reciprocals within one: against 64 bits, g and the gradient are as far off as with the library's expf and IEEE
+// divisions, at 59 VALU instructions instead of 105, which bound the epilogue (205 M values at 16 x 512^2 x
+// 49). The bare hardware functions (20 instructions; a training step 1.99 ms instead of 2.04) put r and the
+// gradient about a fifth to a third further off.
 struct GateLoss {
-    float l2e_t;  // log2(e) / T
-    float c;      // -2 loss_scale / T
+    float ehi, elo;  // log2(e) / T
+    float c;         // -2 loss_scale / T
 };
 __device__ __forceinline__ void gate_loss(float o, float z, float zc, const GateLoss& gl, float& lsum, float& v) {
-    constexpr float L2E = 1.44269504088896341f, LN2 = 0.693147180559945309f;
-    const float u = __builtin_amdgcn_exp2f(-fabsf(o) * L2E), w = 1.0f + u, rw = __builtin_amdgcn_rcpf(w);
-    const float tau = fmaf(__builtin_amdgcn_logf(w), LN2, o > 0.0f ? o : 0.0f);
-    const float so = (o > 0.0f ? 1.0f : u) * rw;
-    const float g = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f((tau - fabsf(z)) * gl.l2e_t));
-    const float zg = z * g, r = zg - zc;
+    constexpr float L2E = 1.44269504088896341f, L2E_LO = (float)(1.44269504088896340736 - (double)L2E);
+    const float u = exp2_product(-fabsf(o), L2E, L2E_LO);
+    const float tau = softplus_of(o, u);
+    const float so = (o > 0.0f ? 1.0f : u) * rcp_newton(1.0f + u);
+    const float g = rcp_newton(1.0f + exp2_product(tau - fabsf(z), gl.ehi, gl.elo));
+    const float r = fmaf(z, g, -zc);
     lsum = fmaf(r, r, lsum);
-    v = gl.c * r * zg * (1.0f - g) * so;
+    v = gl.c * r * (z * g) * (1.0f - g) * so;
 }
 
 // Stages the halo tile of one image from bfloat16 channel-last activations with C channels per pixel.
@@ -301,7 +321,7 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
         __syncthreads();
         __shared__ float s_loss[THREADS / 64];
         float lsum = 0.0f;
-        const GateLoss gl = {1.44269504088896341f / a.temperature, -2.0f * a.loss_scale / a.temperature};
+        const GateLoss gl = {a.gate_ehi, a.gate_elo, a.gate_c};
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
             const int prow = (2 * w + mt / 2) * TW + (mt % 2) * 16 + lm;
