@@ -908,6 +908,12 @@ __global__ __launch_bounds__((SCfg<NG>::THREADS), 3) void k_conv_shrink(ConvArgs
             }
         }
         if (lp_copy && threadIdx.x < PTH * PTW / 4) {
+            if constexpr (TAU) {
+                // the decision with a threshold of 0 that the other planes' lanes take (a NaN is not kept)
+                const float ls = a.scale[b * K + K - 1];
+                auto kept = [ls](float v) { return fabsf(v * ls) >= 0.0f ? v : 0.0f; };
+                lp = make_float4(kept(lp.x), kept(lp.y), kept(lp.z), kept(lp.w));
+            }
             *reinterpret_cast<float4*>(a.out_f + lpo) = lp;
             if constexpr (TAU) *reinterpret_cast<float4*>(a.tau + lpo) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
