@@ -1006,9 +1006,10 @@ int shear_autotune(shear_system* s, int batch, int* pw_fwd, int* pw_inv, int* kg
     if ((long long)batch * (s->cols / 2 / 8) < (long long)s->cus)
         for (int kg : {16, 32})
             if (kg <= s->K) kgs_fwd.push_back(kg);
-    // the workspace and chunk of the largest filter split (its partial sums need the most room)
+    // the workspace and chunk of the largest filter split (its partial sums need the most room), the current
+    // one of the inverse, which the forward's candidates run with, among them
     const shear::DevPlan saved = s->plan;
-    s->plan.kg_inv = kgs.back();
+    s->plan.kg_inv = std::max(s->plan.kg_inv, kgs.back());
     int chunk = 0;
     rc = prepare_ws(s, batch, chunk);
     s->plan = saved;
