@@ -326,10 +326,11 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
  *     shear_forward_noalloc), and pw_fwd = 8 or 16 returns shear_forward to
  *     it. The column IFFT then runs as 16 x 16 (four steps), so results agree
  *     with the panel form to rounding; kg_fwd and pc_fwd do not apply to it;
- *   kg_fwd / kg_inv: filter groups (1..K: the K filters of a column panel are
- *     split over that many blocks, so that small batches fill the device; the
- *     inverse then adds the groups' partial sums in group order). Until it is
- *     set here or by shear_autotune, kg_fwd follows the batch of each call;
+ *   kg_fwd / kg_inv: filter groups (1..K: above 1, the K filters of a column
+ *     panel are split over that many blocks; the inverse then adds the groups'
+ *     partial sums in group order). 1, the value of a new system, leaves the
+ *     split to the library, which follows the batch of each call: in the
+ *     forward over blocks, in the inverse within them (none at 2048 rows);
  *   pc_fwd / pc_inv: points per thread of the rows-point column FFTs, i.e.
  *     their radix sequence: the default (8 up to 512 points, 16 at 1024 and
  *     2048) or, at 256 and 512 points, 16 (two radix-16 passes), at 1024

@@ -401,8 +401,8 @@ class ShearletSystem:
     # ------------------------------------------------------------ column-pass schedule
     def set_schedule(self, pw_fwd: int = 0, pw_inv: int = 0, kg_fwd: int = 0, kg_inv: int = 0, pc_fwd: int = 0,
                      pc_inv: int = 0) -> None:
-        """Columns per block, filter groups and points per thread (radix sequence) of the forward and
-        inverse column passes (shear_set_schedule); 0 keeps a value."""
+        """Columns per block, filter groups (1: by the batch of each call) and points per thread (radix
+        sequence) of the forward and inverse column passes (shear_set_schedule); 0 keeps a value."""
         _check(self._lib.shear_set_schedule(self._h, int(pw_fwd), int(pw_inv), int(kg_fwd), int(kg_inv), int(pc_fwd),
                                             int(pc_inv)), "shear_set_schedule")
 

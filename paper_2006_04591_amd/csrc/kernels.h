@@ -18,7 +18,7 @@ struct DevPlan {
     int cus = 1;              // compute units of the device
     int pw_fwd = 8;           // columns per block of the forward column pass (16 or 8; 8 when L < 16)
     int pw_inv = 16;          // column FFTs per block of the inverse (16 or 8): columns x groups of filters
-    int kg_fwd = 0;           // filter groups of the forward (blocks per panel; capped at K), 0: by batch
+    int kg_fwd = 1;           // filter groups of the forward (blocks per panel; capped at K), 1: by batch
     int kg_inv = 1;           // filter groups over blocks of the inverse (partial sums in memory)
     int pc_fwd = 0;           // points per thread of the column FFTs (0: col_points_default(N); else
     int pc_inv = 0;           // col_points_alternative(N), a different radix sequence)

@@ -980,13 +980,13 @@ inline void kgroups(int K, int kg_req, int& kper, int& kg) {
     kg = (K + kper - 1) / kper;
 }
 
-// Filter groups of the forward column pass where the plan leaves them open (kg_fwd 0): as many as give
-// the device 512 threads per compute unit. A group costs the panel's column FFT again, so a batch
+// Filter groups of the forward column pass where the plan asks for no number of them (kg_fwd 1): as many as
+// give the device 512 threads per compute unit. A group costs the panel's column FFT again, so a batch
 // whose panels alone do that is not split. Measured in 8-column panels (us; groups): one 512 x 512 image
 // of 49 filters 1: 85, 8: 17.0, 16: 18.3, 49: 33.5, four 2: 45.7, 8: 49.3; 256 x 256 x 33 one image 1: 39,
 // 33: 8.8, eight 4: 17.2, 8: 20.9, thirty-two 1: 57.5, 8: 63.1; three 1024 x 1024 x 49 1: 127, 4: 147.
 inline int fwd_groups(const DevPlan& d, int panels, int threads) {
-    if (d.kg_fwd > 0) return d.kg_fwd;
+    if (d.kg_fwd > 1) return d.kg_fwd;
     const long long have = (long long)panels * threads, want = 512LL * d.cus;
     return (int)std::min<long long>(d.K, std::max<long long>(1, (want + have / 2) / have));
 }

@@ -993,11 +993,11 @@ int shear_autotune(shear_system* s, int batch, int* pw_fwd, int* pw_inv, int* kg
     // there is one
     std::vector<int> pcs = {shear::col_points_default(s->rows)};
     if (shear::col_points_alternative(s->rows)) pcs.push_back(shear::col_points_alternative(s->rows));
-    // filter splits over blocks: the forward, which needs no partial sums, tries up to 8 groups, and 16
-    // and 32 when the batch's panels alone (at 8 columns) would leave the device's compute units idle. The
-    // inverse splits the filters within its blocks by itself (launch_cols_inv), which was faster than
-    // partial sums at every size and batch measured; only 2048-point columns, whose blocks cannot, try up
-    // to 8 groups (each adds a partial-sum plane per image).
+    // filter splits over blocks: the forward, which needs no partial sums, tries its own number of groups for
+    // the batch (1), up to 8, and 16 and 32 when the batch's panels alone (at 8 columns) would leave the
+    // device's compute units idle. The inverse splits the filters within its blocks by itself
+    // (launch_cols_inv), which was faster than partial sums at every size and batch measured; only
+    // 2048-point columns, whose blocks cannot, try up to 8 groups (each adds a partial-sum plane per image).
     std::vector<int> kgs, kgs_fwd;
     for (int kg : {1, 2, 4, 8})
         if (kg <= s->K) kgs.push_back(kg);
