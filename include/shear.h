@@ -346,12 +346,14 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
 int shear_set_schedule(shear_system* s, int pw_fwd, int pw_inv, int kg_fwd, int kg_inv, int pc_fwd, int pc_inv);
 
 /* Autotuner: chooses the column-pass schedule of each direction among every
- * compiled panel width, filter split in {1, 2, 4, 8} (at most K; the forward
+ * panel width that selects kernels of its own (16 and 8 below 1024 rows, 8 from
+ * there on), filter groups in {1, 2, 4, 8} (at most K; 1 is the split by batch of
+ * shear_set_schedule, and stays so for calls with other batches; the forward
  * also tries 16 and 32 when batch * cols/16 is below the device's compute
- * units; the inverse only at 2048 rows, as its blocks split the filters
- * themselves below that) and points per thread (default and alternative, where there is one),
- * and for the forward also the whole-plane form where it is compiled.
- * Each candidate is timed inside whole shear_forward + shear_inverse steps at
+ * units; the inverse tries more than 1 only at 2048 rows, as its blocks split the
+ * filters themselves below that) and points per thread (default and
+ * alternative, where there is one), and for the forward also the whole-plane
+ * form where it is compiled. Each candidate is timed inside whole shear_forward + shear_inverse steps at
  * this batch size (the forward's candidates with the current inverse schedule,
  * then the inverse's with the chosen forward), on temporary images and
  * coefficients it allocates for the call (batch * (2 + K) * rows * cols

@@ -987,8 +987,9 @@ int shear_autotune(shear_system* s, int batch, int* pw_fwd, int* pw_inv, int* kg
                    int* pc_inv) {
     int rc = check_call(s, s, s, batch);
     if (rc != SHEAR_OK) return rc;
+    // (from 1024 rows on, 16 would select the same kernels as 8)
     std::vector<int> pws = {8};
-    if (s->cols / 2 >= 16) pws.insert(pws.begin(), 16);
+    if (s->cols / 2 >= 16 && s->rows < 1024) pws.insert(pws.begin(), 16);
     // points per thread of the column FFTs (the radix sequence): the default, and the alternative where
     // there is one
     std::vector<int> pcs = {shear::col_points_default(s->rows)};
