@@ -341,8 +341,8 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
  * current value. The forward's results do not depend on the panel width or
  * the filter split (every column and filter goes through the same
  * operations); the points per thread and, in the inverse, the summation order
- * over the filters (the width too, through the groups) change the rounding, so
- * results agree to rounding. Drops any captured inpainting graph. */
+ * over the filters change the rounding, so results agree to rounding.
+ * Drops any captured inpainting graph. */
 int shear_set_schedule(shear_system* s, int pw_fwd, int pw_inv, int kg_fwd, int kg_inv, int pc_fwd, int pc_inv);
 
 /* Autotuner: chooses the column-pass schedule of each direction among every

@@ -551,10 +551,7 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_fwd(const
 // A block takes PW columns; its G thread groups (PW N/P threads each) take every G-th filter of the
 // block's range k0 + i, and their sums are added in LDS in group order. G > 1 lets a block take fewer
 // columns with as many threads, so that a small batch's columns alone give every compute unit a block
-// and its K filters pass in K/G steps (inv_width chooses). The filters are dealt so that the last one, the
-// low-pass plane with most of an image's energy, is the last of the group added last: taken first, every later
-// addition rounds at its size (the sum over 49 filters in 16 groups, against 64 bits: 1.7e-7 that way, 3.8e-8
-// this way, 4.2e-8 one after the other; 512 x 512 cartoon with noise).
+// and its K filters pass in K/G steps (inv_width chooses).
 template <int N, int PW, int PP, int G>
 struct ColInvCfg {
     static constexpr int P = PP;
