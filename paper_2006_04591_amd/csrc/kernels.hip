@@ -551,7 +551,10 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_fwd(const
 // A block takes PW columns; its G thread groups (PW N/P threads each) take every G-th filter of the
 // block's range k0 + i, and their sums are added in LDS in group order. G > 1 lets a block take fewer
 // columns with as many threads, so that a small batch's columns alone give every compute unit a block
-// and its K filters pass in K/G steps (inv_width chooses).
+// and its K filters pass in K/G steps (inv_width chooses). The filters are dealt so that the last one, the
+// low-pass plane with most of an image's energy, is the last of the group added last: taken first, every later
+// addition rounds at its size (the sum over 49 filters in 16 groups, against 64 bits: 1.7e-7 that way, 3.8e-8
+// this way, 4.2e-8 one after the other; 512 x 512 cartoon with noise).
 template <int N, int PW, int PP, int G>
 struct ColInvCfg {
     static constexpr int P = PP;
@@ -582,8 +585,8 @@ __global__ __launch_bounds__((ColInvCfg<N, PW, PP, G>::THREADS)) void k_cols_inv
 #pragma unroll
     for (int q = 0; q < P; ++q) acc[q] = make_float2(0.0f, 0.0f);
     col_inv_begin<N, P>(col, t, smir);
-    const int k1 = min(K, (g + 1) * kper);
-    for (int k = g * kper + kk; k < k1; k += G)
+    const int k0 = g * kper, k1 = min(K, k0 + kper);
+    for (int k = G == 1 ? k0 : k0 + (kk + k1 - k0) % G; k < k1; k += G)
         col_inv_accum<N, P, REAL>(U + ((size_t)b * K + k) * L * N, filt, k, L, col, t, acc, s, smir, twN);
     if constexpr (G > 1) {
         // (a group's last FFT has read its scratch: the wavefront's LDS operations execute in order)
