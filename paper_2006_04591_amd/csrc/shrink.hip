@@ -1320,11 +1320,23 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
     }
     if (layer == 4 || (layer == 5 && c32)) return conv_relu_t<32, GRAD_MASK>(a, batch, st);  // backward data
     if (layer == 5) return conv_relu_t<64, GRAD_MASK>(a, batch, st);
-    // With the thresholds as an output: one-tile blocks of 8 x 32 pixels below half a persistent tile (8 x 64) per
-    // CU, where their number counts (128^2 x 17: 23.3 us for the network against 25.2 persistent at 32
-    // tiles, 24.8 against 25.8 at 64), the persistent kernel from there on (28.5 -> 27.7 us at 128 tiles, 16 x 512^2 x
-    // 49: 1265 -> 1114). Both sum and decide alike, bit by bit.
-    if (a.tau && 2 * batch * (a.N / PTH) * (a.M / PTW) < a.cus) {
+    // With the thresholds as an output the persistent kernel has more to store and to keep in registers (it
+    // spills, see there), and its gain is mostly the low-pass plane's group left out. Where that plane is alone
+    // in its group (17, 33, 49 planes), it runs from two of its 8 x 64 tiles per CU on, with four groups (50 to
+    // 64) from six, else one-tile blocks of 8 x 32. Network with thresholds, us, one-tile / persistent:
+    //   planes   256 tiles     512 tiles     1024 tiles    2048 tiles    8192 tiles
+    //   16       28.8 / 30.9   43.6 / 43.4   74.4 / 73.1   143 / 151     535 / 541
+    //   17       31.1 / 31.6   47.4 / 44.2   80.7 / 74.5   157 / 157     595 / 548
+    //   32       35.6 / 39.0   54.6 / 54.1   96.3 / 108    220 / 224     847 / 852
+    //   33       44.0 / 42.5   63.7 / 59.1   120 / 118     260 / 244     917 / 856
+    //   48       46.9 / 43.3   69.6 / 70.5   155 / 147     302 / 299     1080 / 1095
+    //   49       46.8 / 43.6   73.0 / 71.3   166 / 150     326 / 304     1196 / 1112
+    //   50       49.9 / 54.0   75.3 / 72.1   169 / 171     330 / 312     1205 / 1131
+    //   64       51.0 / 55.7   81.6 / 82.1   197 / 207     390 / 364     1382 / 1338
+    // Both sum and decide alike, bit by bit.
+    const long long tiles = (long long)batch * (a.N / PTH) * (a.M / PTW);
+    const bool alone = K > 1 && K % 16 == 1;
+    if (a.tau && !(alone ? tiles >= 2LL * a.cus : K > 49 && tiles >= 6LL * a.cus)) {
         switch (shrink_coutp(K)) {
             case 16: return conv_t<32, 16, 5>(a, batch, st);
             case 32: return conv_t<32, 32, 5>(a, batch, st);

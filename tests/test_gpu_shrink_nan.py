@@ -16,7 +16,7 @@ def test_low_pass_nan_does_not_depend_on_the_batch(gpu, K):
     from paper_2006_04591_amd import ShearletSystem, ShrinkNet
 
     print(f"case: low-pass NaN K={K}", flush=True)
-    N, B = 128, 8
+    N, B = 128, 16  # 512 tiles: the persistent kernel at 17, 33 and 49 planes (two tiles per CU, 256 CUs)
     rng = np.random.default_rng(K)
     S = np.fft.fft2(rng.standard_normal((K, N, N)))
     rms = np.sqrt(np.mean(np.abs(S) ** 2, axis=(1, 2)))
