@@ -1070,7 +1070,8 @@ hipError_t cols_fwd_pc(const DevPlan& d, const float2* A, float2* T, int nimg, c
 }
 
 // Columns per block of the inverse column pass, for blocks of S FFTs (S / PW groups of filters): the most
-// that still give the device 768 threads per compute unit (1024 points: 512, and 1024 above 2 columns).
+// that still give the device 768 threads per compute unit (1024 points: 512, and 1024 above 2 columns; short
+// FFTs below).
 // Measured inside forward + inverse steps (us, columns x groups):
 //   512 x 512 x 49, 1 image   1 x 16: 19.5   2 x 8: 23.7   4 x 4: 36.8   8 x 2: 60.3   16 x 1: 113
 //                   4 images  1 x 16: 66.0   2 x 8: 50.7   4 x 4: 44.5   8 x 2: 64.6   16 x 1: 116
@@ -1086,10 +1087,20 @@ hipError_t cols_fwd_pc(const DevPlan& d, const float2* A, float2* T, int nimg, c
 // The rule takes the call's whole batch, not a chunk of it, so that chunks sum in the same order.
 template <int N, int T, int S>
 int inv_width(const DevPlan& d, int batch) {
-    constexpr int lo = T >= 32 ? 1 : 2, hi = N >= 1024 ? 4 : S;
+// Short FFTs want fewer threads, as a block's last steps weigh more: 64 points with a complex bank 512 per
+// compute unit, up to 32 points 256, not below 4 columns, and a block of less than half a wavefront counts as half
+// of one (us an inverse call, columns per block):
+//   64 x 64 x 9, 512 images     complex  4: 70.1   8: 66.3   16: 63.8     real  4: 64.5   8: 60.8   16: 63.8
+//   32 x 32 x 9, 1024 images    complex  4: 56.0   8: 52.0   16: 51.8     real  4: 53.0   8: 50.2   16: 51.9
+//   16 x 64 x 9, 256 images     complex  2: 23.8   4: 22.5    8: 20.7    16: 23.3   (1024: 65.5   61.0   54.4   52.7)
+//   16 x 16 x 5, 2048 images    complex  2: 32.5   4: 29.3    8: 24.3
+    constexpr int lo = T >= 32 ? 1 : (N <= 32 ? 4 : 2), hi = N >= 1024 ? 4 : S;
     int pw = std::min(hi, d.L);
-    auto want = [&] { return (N >= 1024 ? (pw > 2 ? 1024LL : 512LL) : 768LL) * d.cus; };
-    while (pw > lo && (long long)batch * (d.L / pw) * (S * T) < want()) pw /= 2;
+    auto want = [&] {
+        if (N >= 1024) return (pw > 2 ? 1024LL : 512LL) * d.cus;
+        return (N <= 32 ? 256LL : (N == 64 && !d.real ? 512LL : 768LL)) * d.cus;
+    };
+    while (pw > lo && (long long)batch * (d.L / pw) * std::max(S * T, 32) < want()) pw /= 2;
     return pw;
 }
 
@@ -1103,7 +1114,9 @@ hipError_t cols_inv_s(const DevPlan& d, const float2* U, float2* V, int nimg, in
             case 1:
                 if constexpr (T >= 32) return cols_inv_t<N, 1, PP, S>(d, U, V, nimg, filt, part, st);
                 break;
-            case 2: return cols_inv_t<N, 2, PP, S / 2>(d, U, V, nimg, filt, part, st);
+            case 2:
+                if constexpr (N > 32) return cols_inv_t<N, 2, PP, S / 2>(d, U, V, nimg, filt, part, st);
+                break;
             case 4: return cols_inv_t<N, 4, PP, S / 4>(d, U, V, nimg, filt, part, st);
             case 8:
                 if constexpr (N < 1024) return cols_inv_t<N, 8, PP, S / 8>(d, U, V, nimg, filt, part, st);
