@@ -988,9 +988,12 @@ inline void kgroups(int K, int kg_req, int& kper, int& kg) {
 // whose panels alone do that is not split. Measured in 8-column panels (us; groups): one 512 x 512 image
 // of 49 filters 1: 85, 8: 17.0, 16: 18.3, 49: 33.5, four 2: 45.7, 8: 49.3; 256 x 256 x 33 one image 1: 39,
 // 33: 8.8, eight 4: 17.2, 8: 20.9, thirty-two 1: 57.5, 8: 63.1; three 1024 x 1024 x 49 1: 127, 4: 147.
+// FFTs of up to 64 points, with few threads each and less work to a group: 256 threads, a block of less
+// than half a wavefront counted as half of one (16-column panels, us a forward call: 64 x 64 x 9, 128 images 1: 24.5,
+// 2: 22.4, 4: 23.3, 256 images 1: 38.3, 2: 42.3; 16 x 64 x 9, 1024 images 1: 50.4, 2: 51.6).
 inline int fwd_groups(const DevPlan& d, int panels, int threads) {
     if (d.kg_fwd > 1) return d.kg_fwd;
-    const long long have = (long long)panels * threads, want = 512LL * d.cus;
+    const long long have = (long long)panels * std::max(threads, 32), want = (d.N <= 64 ? 256LL : 512LL) * d.cus;
     return (int)std::min<long long>(d.K, std::max<long long>(1, (want + have / 2) / have));
 }
 
