@@ -314,9 +314,11 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
 
 /* Column-pass schedule of the separate-launch kernels:
  *   pw_fwd / pw_inv: column FFTs per block (16 or 8; 16 needs cols >= 32). In the
- *     forward they are that many columns; in the inverse, columns times groups
- *     of filters whose sums the block adds, fewer columns and more groups the
- *     fewer columns the call has (8 FFTs at 1024 points either way);
+ *     forward they are that many columns (4 from 1024 rows on, whichever is
+ *     set); in the inverse, columns times groups of filters whose sums the
+ *     block adds, fewer columns and more groups the fewer columns the call has
+ *     (8 FFTs at 1024 rows, 4 columns and no groups at 2048, whichever is set),
+ *     or, with kg_inv above 1, columns alone;
  *     pw_fwd = cols / 2 (the whole packed plane per workgroup) selects, for
  *     shear_forward, the whole-plane forward where it is compiled (256 x 256
  *     systems with real filter sets): one workgroup filters a plane,
@@ -334,8 +336,8 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
  *   pc_fwd / pc_inv: points per thread of the rows-point column FFTs, i.e.
  *     their radix sequence: the default (8 up to 512 points, 16 at 1024 and
  *     2048) or, at 256 and 512 points, 16 (two radix-16 passes), at 1024
- *     points, 8 (a 128-thread FFT group over two wavefronts; with 16-column
- *     blocks, which would need 2048 threads, the default runs instead);
+ *     points, 8 (a 128-thread FFT group over two wavefronts; with a width of
+ *     16 set, the default runs instead);
  *     SHEAR_E_INVALID for any other value at that size;
  * in the forward and in the inverse/adjoint column passes; 0 keeps the
  * current value. The forward's results do not depend on the panel width or

@@ -1112,7 +1112,7 @@ hipError_t cols_inv_s(const DevPlan& d, const float2* U, float2* V, int nimg, in
                       hipStream_t st) {
     constexpr int T = N / PP;
     if constexpr (T <= 64) {
-        if (d.kg_inv > 1) return cols_inv_t<N, 8, PP, 1>(d, U, V, nimg, filt, part, st);
+        if (d.kg_inv > 1) return cols_inv_t<N, S, PP, 1>(d, U, V, nimg, filt, part, st);
         switch (inv_width<N, T, S>(d, batch)) {
             case 1:
                 if constexpr (T >= 32) return cols_inv_t<N, 1, PP, S>(d, U, V, nimg, filt, part, st);
