@@ -146,7 +146,15 @@ int shear_forward(shear_system* s, const float* x, float* coeffs, int batch, voi
 int shear_forward_noalloc(shear_system* s, const float* x, float* coeffs, int batch, void* hip_stream);
 
 /* tfshearrec2D / Algorithm 2 (Section 3.4.2): coeffs -> x, dividing the
- * filtered sum by the dual-frame weight W. Asynchronous. */
+ * filtered sum by the dual-frame weight W. Asynchronous.
+ * The order in which the K filters are summed, here and in shear_adjoint,
+ * shear_denoise, shear_inpaint and shear_inpaint_groups, follows the number of
+ * images in the call and the device's compute units: the same image alone and
+ * in a batch gives results that agree to FP32 rounding, not bit for bit (in
+ * inpainting the decision on a coefficient that rounding moves across its
+ * threshold follows). Equal calls give equal bits, and chunks that
+ * max_workspace_bytes forces leave them as they are. With a kg_inv above 1
+ * (shear_set_schedule) the order is the same at every batch. */
 int shear_inverse(shear_system* s, const float* coeffs, float* x, int batch, void* hip_stream);
 
 /* Adjoint SH* of shear_forward (Algorithm 2 without the division by W):
@@ -343,8 +351,8 @@ int shear_profile_read(shear_system* s, int* launches, double* total_ms);
  * current value. The forward's results do not depend on the panel width or
  * the filter split (every column and filter goes through the same
  * operations); the points per thread and, in the inverse, the summation order
- * over the filters change the rounding, so results agree to rounding.
- * Drops any captured inpainting graph. */
+ * over the filters (the width too, through the groups) change the rounding, so
+ * results agree to rounding. Drops any captured inpainting graph. */
 int shear_set_schedule(shear_system* s, int pw_fwd, int pw_inv, int kg_fwd, int kg_inv, int pc_fwd, int pc_inv);
 
 /* Autotuner: chooses the column-pass schedule of each direction among every
