@@ -1087,9 +1087,6 @@ hipError_t cols_fwd_pc(const DevPlan& d, const float2* A, float2* T, int nimg, c
 // Splitting the filters over blocks with partial sums in memory (kg_inv 2 to 8) was slower throughout
 // (28.3 at best for one 512 x 512 image, 28.0 and 66.4 for 8 and 32 of 256 x 256). Not below 2 columns
 // where an FFT is less than half a wavefront (128 x 128 x 17, 4 images: 2 x 8 9.1, 1 x 16 9.9).
-// The rule takes the call's whole batch, not a chunk of it, so that chunks sum in the same order.
-template <int N, int T, int S>
-int inv_width(const DevPlan& d, int batch) {
 // Short FFTs want fewer threads, as a block's last steps weigh more: 64 points with a complex bank 512 per
 // compute unit, up to 32 points 256, not below 4 columns, and a block of less than half a wavefront counts as half
 // of one (us an inverse call, columns per block):
@@ -1097,6 +1094,9 @@ int inv_width(const DevPlan& d, int batch) {
 //   32 x 32 x 9, 1024 images    complex  4: 56.0   8: 52.0   16: 51.8     real  4: 53.0   8: 50.2   16: 51.9
 //   16 x 64 x 9, 256 images     complex  2: 23.8   4: 22.5    8: 20.7    16: 23.3   (1024: 65.5   61.0   54.4   52.7)
 //   16 x 16 x 5, 2048 images    complex  2: 32.5   4: 29.3    8: 24.3
+// The rule takes the call's whole batch, not a chunk of it, so that chunks sum in the same order.
+template <int N, int T, int S>
+int inv_width(const DevPlan& d, int batch) {
     constexpr int lo = T >= 32 ? 1 : (N <= 32 ? 4 : 2), hi = N >= 1024 ? 4 : S;
     int pw = std::min(hi, d.L);
     auto want = [&] {

@@ -12,10 +12,11 @@
 // holds A row l%16 and B column l%16 with k = 8(l/16) .. 8(l/16)+7, and D
 // column l%16 with rows 4(l/16) .. 4(l/16)+3.
 //
-// A block computes a tile of TH x TW = 8 x 32 output pixels of one image for
-// all output channels. Its input tile with a one-pixel halo (wrapped around
-// the plane) is staged in LDS channel-last, one padded run of channels per
-// pixel, so that a lane's 8 consecutive k of one tap are one 16-byte read.
+// A block of k_conv3x3 computes a tile of TH x TW = 8 x 32 output pixels of one
+// image for all output channels; the persistent kernels walk tiles of 8 x 64 or
+// 4 x 128. An input tile with a one-pixel halo (wrapped around the plane) is
+// staged in LDS channel-last, one padded run of channels per pixel, so that a
+// lane's 8 consecutive k of one tap are one 16-byte read.
 // Hidden activations are stored channel-last in bfloat16: [b][y][x][32].
 #include "shrink.h"
 
@@ -583,8 +584,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     using L = PLds<CS, FROM_COEF>;
     constexpr int TH = L::TH, TW = L::TW, HH = L::HH, HW = L::HW;
     constexpr int R0 = SLIDE ? 2 : 0, NR = HH - R0;  // staged rows loaded per tile (the prefetch)
-    using Regs8 = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR, CS>>::type;
-    using Regs2 = typename std::conditional<FROM_COEF, CoefRegs<CS, 2>, HidRegs<2, CS>>::type;
+    using Regs = typename std::conditional<FROM_COEF, CoefRegs<CS, NR>, HidRegs<NR, CS>>::type;
     // the scales of the lane's 8 channels, of image bsc; they are loaded where the image changes, and waited for
     // there, so that no wait for them holds up a tile's loads
     [[maybe_unused]] float sc[8];
@@ -595,29 +595,24 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 #pragma unroll
         for (int c = 0; c < 8; ++c) asm volatile("" : "+v"(sc[c]));
     };
-    auto load8 = [&](Regs8& r, int b, int y0, int x0) {  // staged rows R0 .. 9
+    auto load_rows = [&](Regs& r, int b, int y0, int x0) {  // staged rows R0 .. HH - 1
         if constexpr (FROM_COEF) {
             coef_load<CS, NR>(a, r, b, y0, x0, R0);
         } else {
             hid_load<NR, CS>(a, r, b, y0, x0, R0);
         }
     };
-    auto store8 = [&](const Regs8& r, unsigned short* s, [[maybe_unused]] int rb) {
+    auto store_rows = [&](const Regs& r, unsigned short* s, [[maybe_unused]] int rb) {
         if constexpr (FROM_COEF) {
             coef_store<CS, NR>(r, sc, s, R0, rb);
         } else {
             hid_store<NR, CS>(r, s, R0);
         }
     };
-    auto stage_top = [&](unsigned short* s, int b, int y0, int x0, [[maybe_unused]] int rb) {  // rows 0, 1 from memory
-        Regs2 r2;
-        if constexpr (FROM_COEF) {
-            coef_load<CS, 2>(a, r2, b, y0, x0, 0);
-            coef_store<CS, 2>(r2, sc, s, 0, rb);
-        } else {
-            hid_load<2, CS>(a, r2, b, y0, x0, 0);
-            hid_store<2, CS>(r2, s, 0);
-        }
+    [[maybe_unused]] auto stage_top = [&](unsigned short* s, int b, int y0, int x0, int rb) {  // rows 0, 1 (SLIDE)
+        CoefRegs<CS, 2> r2;
+        coef_load<CS, 2>(a, r2, b, y0, x0, 0);
+        coef_store<CS, 2>(r2, sc, s, 0, rb);
     };
     extern __shared__ unsigned short smem[];
     unsigned short* s_in = smem;
@@ -657,19 +652,19 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
     }
     int rb = 0;  // ring slot of staged row 0 (SLIDE)
     auto slot = [&](int yy) { return !SLIDE || yy + rb < HH ? yy + rb : yy + rb - HH; };
-    Regs8 r;
+    Regs r;
     int b, y0, x0;
     tile_origin(t, b, y0, x0);
     if constexpr (SLIDE) {
         scales(b);
         stage_top(s_in, b, y0, x0, rb);
     }
-    load8(r, b, y0, x0);
-    store8(r, s_in, rb);
+    load_rows(r, b, y0, x0);
+    store_rows(r, s_in, rb);
     if (t + stride < end) {
         int bn, yn, xn;
         tile_origin(t + stride, bn, yn, xn);
-        load8(r, bn, yn, xn);
+        load_rows(r, bn, yn, xn);
     }
     __syncthreads();
     for (;;) {
@@ -683,7 +678,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
                     *reinterpret_cast<const uint4*>(s_in + (slot(py + 1) * HW + px + 1) * PIX + ch * 8);
             }
         }
-        // wave w: tile row w, 4 m-tiles of 16 pixels
+        // a wavefront: 64 pixels of tile row wr, 4 m-tiles of 16
         f32x4 acc[4][2];
         zero_acc(acc);
 #pragma unroll 1
@@ -747,7 +742,7 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
         int bq, yq, xq;
         tile_origin(more ? tn + stride : tn, bq, yq, xq);
         if constexpr (SLIDE) {
-            constexpr int NIT = Regs8::NIT;
+            constexpr int NIT = Regs::NIT;
             coef_store<CS, NR, NIT>(r, sc, s_in, R0, rb);
             if (more) coef_load<CS, NR, NIT>(a, r, bq, yq, xq, R0);
             coef_store<CS, NR, 0>(r, sc, s_in, R0, rb);
@@ -757,8 +752,8 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
                 if (more) coef_load<CS, NR, 1>(a, r, bq, yq, xq, R0);
             }
         } else {
-            store8(r, s_in, rb);
-            if (more) load8(r, bq, yq, xq);
+            store_rows(r, s_in, rb);
+            if (more) load_rows(r, bq, yq, xq);
         }
         t = tn;
         b = bn;
@@ -769,9 +764,9 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 }
 
 // ---------------------------------------------------------------- persistent shrink layer
-// The last layer with the shrink decision (and, TAU, the thresholds it is taken with), persistent: two or three blocks per CU walk their
-// XCD's range of 8 x 64-pixel tiles. A wavefront keeps the weights of one group of 16 output channels in
-// registers (36 VGPRs) and takes PTH / RH rows of the tile: per row, 4 m-tiles of 16 pixels x 9 taps of
+// The last layer with the shrink decision (and, TAU, the thresholds it is taken with), persistent: two or three
+// blocks per CU walk their XCD's range of 8 x 64-pixel tiles. A wavefront keeps the weights of one group of 16
+// output channels in registers (36 VGPRs) and takes PTH / RH rows of the tile: per row, 4 m-tiles of 16 pixels x 9 taps of
 // products out of the staged activations, then the decision on the row's coefficients where the matrix
 // cores leave the outputs (a lane holds 4 consecutive pixels of one channel: 16-byte loads and stores in
 // 64-byte runs, two of them to a line), with the next row's coefficients in flight. Nothing but the
@@ -780,7 +775,11 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 // The low-pass plane, the last, is kept whole: where it would be alone in its group (K = 17, 33, 49) it
 // is copied and the group's products and decisions are left out. Per 16 x 512^2 x 49 batch: 0.44-0.46 ms;
 // with the coefficients passed through LDS in three barrier phases per 32 channels, one block per CU,
-// 0.50 ms. What bounds it: 1.64 GB of coefficients in and out and 0.35 GB of activations.
+// 0.50 ms. What bounds it: 1.64 GB of coefficients in and out and 0.35 GB of activations. With 256 threads (one,
+// two and four groups) a thread holds 11 instead of 7 pieces of the next tile's activations, which with the
+// weights pass the 168 registers of three waves per SIMD: 76 to 84 bytes of scratch a lane (three groups: none;
+// with TAU 88 to 120, three groups 20). The network is still faster there than with the phases, which did
+// not spill (8 x 512^2 images: 282 -> 257 us at 17 planes, 424 -> 351 at 33, 570 -> 527 at 64).
 //
 // The decision |c scale| >= tau = softplus(o) is taken without forming tau: with a = |c scale| >= 0,
 // m = max(o, 0), u = e^-|o| in (0, 1] and d = a - m, softplus(o) = m + log1p(u), so a >= softplus(o)
@@ -1354,10 +1353,6 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
     return hipErrorInvalidValue;
 }
 
-}  // namespace shear
-
-namespace shear {
-
 hipError_t launch_wgrad(int layer, int K, const WgradArgs& a, int blocks, hipStream_t st) {
     if (layer == 0) return shrink_cinp(K) == 32 ? wgrad_t<32, 32>(a, blocks, st) : wgrad_t<64, 32>(a, blocks, st);
     if (layer == 1) return wgrad_t<32, 32>(a, blocks, st);
@@ -1398,9 +1393,5 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, floa
                        c2);
     return hipGetLastError();
 }
-
-}  // namespace shear
-
-namespace shear {
 
 }  // namespace shear
