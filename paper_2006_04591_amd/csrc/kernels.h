@@ -16,7 +16,8 @@ struct DevPlan {
     const float2* twL = nullptr;  // exp(-2 pi i m / L), m < L
     const float2* twM = nullptr;  // exp(-2 pi i m / M), m < M
     int cus = 1;              // compute units of the device
-    int pw_fwd = 8;           // columns per block of the forward column pass (16 or 8; 8 when L < 16; as built 16 up to 64 rows)
+    int pw_fwd = 8;           // columns per block of the forward column pass (16 or 8; 8 when L < 16), as
+                              // built 16 up to 64 rows
     int pw_inv = 16;          // column FFTs per block of the inverse (16 or 8): columns x groups of filters
     int kg_fwd = 1;           // filter groups of the forward (blocks per panel; capped at K), 1: by batch
     int kg_inv = 1;           // filter groups over blocks of the inverse (partial sums in memory)

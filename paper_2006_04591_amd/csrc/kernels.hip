@@ -552,9 +552,9 @@ __global__ __launch_bounds__((ColCfg<N, PW, PP>::THREADS)) void k_cols_fwd(const
 // block's range k0 + i, and their sums are added in LDS in group order. G > 1 lets a block take fewer
 // columns with as many threads, so that a small batch's columns alone give every compute unit a block
 // and its K filters pass in K/G steps (inv_width chooses). The filters are dealt so that the last one, the
-// low-pass plane with most of an image's energy, is the last of the group added last: taken first, every later
-// addition rounds at its size (the sum over 49 filters in 16 groups, against 64 bits: 1.7e-7 that way, 3.8e-8
-// this way, 4.2e-8 one after the other; 512 x 512 cartoon with noise).
+// low-pass plane with most of an image's energy, ends the first group, and that group is added last: with the
+// low-pass first, every later addition rounds at its size (the sum over 49 filters in 16 groups, against 64 bits: 1.7e-7
+// that way, 3.8e-8 this way, 4.2e-8 one after the other; 512 x 512 cartoon with noise).
 template <int N, int PW, int PP, int G>
 struct ColInvCfg {
     static constexpr int P = PP;
@@ -586,7 +586,7 @@ __global__ __launch_bounds__((ColInvCfg<N, PW, PP, G>::THREADS)) void k_cols_inv
     for (int q = 0; q < P; ++q) acc[q] = make_float2(0.0f, 0.0f);
     col_inv_begin<N, P>(col, t, smir);
     const int k0 = g * kper, k1 = min(K, k0 + kper);
-    for (int k = G == 1 ? k0 : k0 + (kk + k1 - k0) % G; k < k1; k += G)
+    for (int k = G == 1 ? k0 : k0 + (int)((unsigned)(kk + k1 - 1 - k0) % G); k < k1; k += G)
         col_inv_accum<N, P, REAL>(U + ((size_t)b * K + k) * L * N, filt, k, L, col, t, acc, s, smir, twN);
     if constexpr (G > 1) {
         // (a group's last FFT has read its scratch: the wavefront's LDS operations execute in order)
@@ -598,14 +598,20 @@ __global__ __launch_bounds__((ColInvCfg<N, PW, PP, G>::THREADS)) void k_cols_inv
         __syncthreads();
         if (kk == 0) {
 #pragma unroll
-            for (int i = 1; i < G; ++i)
+            for (int q = 0; q < P; ++q) {
+                float2 o = s[PW * CS + t + T * q];
 #pragma unroll
-                for (int q = 0; q < P; ++q) acc[q] = cadd(acc[q], s[i * PW * CS + t + T * q]);
+                for (int i = 2; i < G; ++i) o = cadd(o, s[i * PW * CS + t + T * q]);
+                acc[q] = cadd(o, acc[q]);
+            }
             if (col == 0) {
 #pragma unroll
-                for (int i = 1; i < G; ++i)
+                for (int q = 0; q < P; ++q) {
+                    float2 o = smir[N + t + T * q];
 #pragma unroll
-                    for (int q = 0; q < P; ++q) smir[t + T * q] = cadd(smir[t + T * q], smir[i * N + t + T * q]);
+                    for (int i = 2; i < G; ++i) o = cadd(o, smir[i * N + t + T * q]);
+                    smir[t + T * q] = cadd(o, smir[t + T * q]);
+                }
             }
         }
     }
