@@ -68,7 +68,7 @@ struct Pix {
 template <int CINP, int OUTC, int MODE>
 constexpr size_t conv_lds_bytes() {
     constexpr size_t in = (size_t)HH * HW * Pix<CINP>::value * 2, out = (size_t)TH * TW * OUTC * 2;
-    return (MODE == 5 || in >= out) ? in : out;
+    return (MODE == 2 || MODE == 5 || in >= out) ? in : out;
 }
 
 // 2^(x c) for c given as the float chi and the rest clo, to about an ulp: the rounding error of x chi and the
@@ -234,7 +234,31 @@ __device__ __forceinline__ int conv_tile() {
     return (w % 8) * per + w / 8;
 }
 
-// MODE 5: activations -> o + b -> shrink of the coefficients where |c scale| >= tau = softplus(o), and tau;
+// The decision |c scale| >= tau = softplus(o) is taken without forming tau: with a = |c scale| >= 0,
+// m = max(o, 0), u = e^-|o| in (0, 1] and d = a - m, softplus(o) = m + log1p(u), so a >= softplus(o)
+// <=> expm1(d) >= u. d is clamped to [0, 0.75] (below 0, expm1 < 0 < u; above, expm1 > 1 >= u), where
+// expm1 is its Taylor polynomial of degree 9 (remainder < 2e-8 relative), and for o > 0, u is kept
+// above 1e-30 (beyond o = 87 it underflows: then softplus(o) = o in FP32 and the test is d > 0). The
+// low-pass plane takes o = -inf: u = 0, every coefficient kept. One hardware exponential replaces
+// softplus's exponential, logarithm and reciprocal, with no branch, and the decision keeps softplus's
+// relative precision for small and large thresholds alike.
+__device__ __forceinline__ float shrink_keep(float v, float sc, float o) {
+    constexpr float L2E = 1.44269504088896341f;
+    const float d = fminf(fmaxf(fabsf(v * sc) - fmaxf(o, 0.0f), 0.0f), 0.75f);
+    const float u = fmaxf(__builtin_amdgcn_exp2f(-fabsf(o) * L2E), o > 0.0f ? 1e-30f : 0.0f);
+    float e = 1.0f / 362880.0f;
+    e = fmaf(e, d, 1.0f / 40320.0f);
+    e = fmaf(e, d, 1.0f / 5040.0f);
+    e = fmaf(e, d, 1.0f / 720.0f);
+    e = fmaf(e, d, 1.0f / 120.0f);
+    e = fmaf(e, d, 1.0f / 24.0f);
+    e = fmaf(e, d, 1.0f / 6.0f);
+    e = fmaf(e, d, 0.5f);
+    e = fmaf(e, d, 1.0f);
+    return (e * d >= u) ? v : 0.0f;
+}
+
+// MODE 2: activations -> o + b -> shrink of the coefficients where |c scale| >= tau = softplus(o); 5: and tau;
 // MODE 3 (training, last layer): o -> smooth-gate loss (each tile's sum to loss[tile]) and its gradient d o,
 //   stored as bf16 channel-last planes [b][y][x][OUTC] (zero beyond COUTP and on the low-pass plane).
 template <int CINP, int COUTP, int MODE, int OUTC = 32>
@@ -245,7 +269,7 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
     const int tx = a.M / TW, ty = a.N / TH, tile = conv_tile();
     const int bx = tile % tx, by = (tile / tx) % ty, b = tile / (tx * ty);
     const int x0 = bx * TW, y0 = by * TH;
-    constexpr bool SHRINK = MODE == 5;
+    constexpr bool SHRINK = MODE == 5 || MODE == 2;
     stage<CINP>(a, s_in, b, y0, x0);
     __syncthreads();
     const int w = threadIdx.x / 64, l = threadIdx.x % 64;
@@ -304,11 +328,16 @@ __global__ __launch_bounds__(THREADS) void k_conv3x3(ConvArgs a) {
                 float t[4], r[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    t[i] = lowpass ? 0.0f : softplusf(acc[mt][nt][i] + bias);
-                    r[i] = (fabsf(v[i] * sc) >= t[i]) ? v[i] : 0.0f;
+                    if constexpr (MODE == 5) {
+                        t[i] = lowpass ? 0.0f : softplusf(acc[mt][nt][i] + bias);
+                        r[i] = (fabsf(v[i] * sc) >= t[i]) ? v[i] : 0.0f;
+                    } else {
+                        r[i] = shrink_keep(v[i], sc, lowpass ? -INFINITY : acc[mt][nt][i] + bias);
+                    }
                 }
                 *reinterpret_cast<float4*>(op + vo) = make_float4(r[0], r[1], r[2], r[3]);
-                *reinterpret_cast<float4*>(a.tau + offs[nt] + vo) = make_float4(t[0], t[1], t[2], t[3]);
+                if constexpr (MODE == 5)
+                    *reinterpret_cast<float4*>(a.tau + offs[nt] + vo) = make_float4(t[0], t[1], t[2], t[3]);
             }
         }
         }
@@ -781,30 +810,6 @@ __global__ __launch_bounds__(PTHREADS, CINP == 32 && KIND >= HID_RELU ? 4 : 2) v
 // with TAU 88 to 120, three groups 20). The network is still faster there than with the phases, which did
 // not spill (8 x 512^2 images: 282 -> 257 us at 17 planes, 424 -> 351 at 33, 570 -> 527 at 64).
 //
-// The decision |c scale| >= tau = softplus(o) is taken without forming tau: with a = |c scale| >= 0,
-// m = max(o, 0), u = e^-|o| in (0, 1] and d = a - m, softplus(o) = m + log1p(u), so a >= softplus(o)
-// <=> expm1(d) >= u. d is clamped to [0, 0.75] (below 0, expm1 < 0 < u; above, expm1 > 1 >= u), where
-// expm1 is its Taylor polynomial of degree 9 (remainder < 2e-8 relative), and for o > 0, u is kept
-// above 1e-30 (beyond o = 87 it underflows: then softplus(o) = o in FP32 and the test is d > 0). The
-// low-pass plane takes o = -inf: u = 0, every coefficient kept. One hardware exponential replaces
-// softplus's exponential, logarithm and reciprocal, with no branch, and the decision keeps softplus's
-// relative precision for small and large thresholds alike.
-__device__ __forceinline__ float shrink_keep(float v, float sc, float o) {
-    constexpr float L2E = 1.44269504088896341f;
-    const float d = fminf(fmaxf(fabsf(v * sc) - fmaxf(o, 0.0f), 0.0f), 0.75f);
-    const float u = fmaxf(__builtin_amdgcn_exp2f(-fabsf(o) * L2E), o > 0.0f ? 1e-30f : 0.0f);
-    float e = 1.0f / 362880.0f;
-    e = fmaf(e, d, 1.0f / 40320.0f);
-    e = fmaf(e, d, 1.0f / 5040.0f);
-    e = fmaf(e, d, 1.0f / 720.0f);
-    e = fmaf(e, d, 1.0f / 120.0f);
-    e = fmaf(e, d, 1.0f / 24.0f);
-    e = fmaf(e, d, 1.0f / 6.0f);
-    e = fmaf(e, d, 0.5f);
-    e = fmaf(e, d, 1.0f);
-    return (e * d >= u) ? v : 0.0f;
-}
-
 // NG groups of 16 output channels
 template <int NG>
 struct SCfg {
@@ -1319,32 +1324,38 @@ hipError_t launch_conv(int layer, int K, const ConvArgs& a, int batch, hipStream
     }
     if (layer == 4 || (layer == 5 && c32)) return conv_relu_t<32, GRAD_MASK>(a, batch, st);  // backward data
     if (layer == 5) return conv_relu_t<64, GRAD_MASK>(a, batch, st);
-    // With the thresholds as an output the persistent kernel has more to store and to keep in registers (it
-    // spills, see there), and its gain is mostly the low-pass plane's group left out. Where that plane is alone
-    // in its group (17, 33, 49 planes), it runs from two of its 8 x 64 tiles per CU on, with four groups (50 to
-    // 64) from six, else one-tile blocks of 8 x 32. Network with thresholds, us, one-tile / persistent:
-    //   planes   256 tiles     512 tiles     1024 tiles    2048 tiles    8192 tiles
-    //   16       28.8 / 30.9   43.6 / 43.4   74.4 / 73.1   143 / 151     535 / 541
-    //   17       31.1 / 31.6   47.4 / 44.2   80.7 / 74.5   157 / 157     595 / 548
-    //   32       35.6 / 39.0   54.6 / 54.1   96.3 / 108    220 / 224     847 / 852
-    //   33       44.0 / 42.5   63.7 / 59.1   120 / 118     260 / 244     917 / 856
-    //   48       46.9 / 43.3   69.6 / 70.5   155 / 147     302 / 299     1080 / 1095
-    //   49       46.8 / 43.6   73.0 / 71.3   166 / 150     326 / 304     1196 / 1112
-    //   50       49.9 / 54.0   75.3 / 72.1   169 / 171     330 / 312     1205 / 1131
-    //   64       51.0 / 55.7   81.6 / 82.1   197 / 207     390 / 364     1382 / 1338
+    // The shrink layer in the persistent kernel or in one-tile blocks of 8 x 32. The persistent kernel's gains are the
+    // low-pass plane's group left out where it is alone (17, 33, 49 planes) and less staging and weight traffic;
+    // a short call pays for its serial rows and, with one, two and four groups, its spills. So without the
+    // thresholds it takes 17 and 33 to 49 planes always, two and four groups from 512 and 256 of its 8 x 64
+    // tiles on (2 / groups to a CU), and none of up to 16 planes. With them, which it has to store and to keep
+    // in registers, it takes 17, 33 and 49 planes from two tiles per CU on, 50 to 64 from six. The network, us, one-tile /
+    // persistent, without and with thresholds:
+    //   planes   128 tiles                  256 tiles                  512 tiles                  2048 tiles
+    //   16       21.4 / 23.7  22.6 / 25.9   28.2 / 29.2  30.3 / 32.1   39.8 / 39.8  43.0 / 42.8   115 / 115  134 / 138
+    //   17       24.4 / 23.7  23.8 / 26.4   32.2 / 29.6  32.7 / 33.0   45.2 / 40.2  46.6 / 43.7   129 / 121  152 / 149
+    //   32       24.2 / 28.5  28.6 / 34.8   33.8 / 34.6  37.5 / 40.5   49.5 / 46.3  54.1 / 53.7   173 / 176  215 / 228
+    //   33       32.0 / 31.7  35.9 / 38.0   42.3 / 37.6  44.4 / 43.8   59.6 / 51.4  63.0 / 58.8   212 / 191  254 / 243
+    //   48       34.1 / 34.3  40.4 / 39.6   44.3 / 40.1  47.9 / 44.3   62.8 / 61.7  69.7 / 70.6   237 / 223  296 / 296
+    //   49       37.0 / 34.4  39.5 / 40.2   46.5 / 40.4  48.6 / 45.0   67.9 / 62.4  72.6 / 71.1   256 / 226  322 / 306
+    //   50       37.8 / 41.3  42.2 / 50.0   46.9 / 46.4  50.4 / 55.0   67.8 / 62.1  75.0 / 71.2   258 / 231  325 / 308
+    //   64       38.4 / 43.1  43.5 / 52.4   49.1 / 49.0  54.4 / 58.9   72.4 / 67.1  82.8 / 81.8   308 / 288  418 / 382
     // Both sum and decide alike, bit by bit.
     const long long tiles = (long long)batch * (a.N / PTH) * (a.M / PTW);
+    const int groups = std::max(1, (K - 1 + 15) / 16);  // groups of 16 channels up to the low-pass plane
     const bool alone = K > 1 && K % 16 == 1;
-    if (a.tau && !(alone ? tiles >= 2LL * a.cus : K > 49 && tiles >= 6LL * a.cus)) {
+    const bool persistent = a.tau ? (alone ? tiles >= 2LL * a.cus : groups == 4 && tiles >= 6LL * a.cus)
+                                  : (alone || groups == 3 || (groups > 1 && tiles * groups >= 4LL * a.cus));
+    if (!persistent) {
         switch (shrink_coutp(K)) {
-            case 16: return conv_t<32, 16, 5>(a, batch, st);
-            case 32: return conv_t<32, 32, 5>(a, batch, st);
-            case 48: return conv_t<32, 48, 5>(a, batch, st);
-            case 64: return conv_t<32, 64, 5>(a, batch, st);
+            case 16: return a.tau ? conv_t<32, 16, 5>(a, batch, st) : conv_t<32, 16, 2>(a, batch, st);
+            case 32: return a.tau ? conv_t<32, 32, 5>(a, batch, st) : conv_t<32, 32, 2>(a, batch, st);
+            case 48: return a.tau ? conv_t<32, 48, 5>(a, batch, st) : hipErrorInvalidValue;  // (without: persistent)
+            case 64: return a.tau ? conv_t<32, 64, 5>(a, batch, st) : conv_t<32, 64, 2>(a, batch, st);
         }
         return hipErrorInvalidValue;
     }
-    switch (std::max(1, (K - 1 + 15) / 16)) {  // groups of 16 channels up to the low-pass plane
+    switch (groups) {
         case 1: return conv_shrink_t<1>(a, batch, st);
         case 2: return conv_shrink_t<2>(a, batch, st);
         case 3: return conv_shrink_t<3>(a, batch, st);
