@@ -42,17 +42,17 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
     return (unsigned short)(u >> 16);
 }
 
-// softplus(x) = max(x, 0) + log1p(u), u = e^{-|x|} in (0, 1], with the hardware logarithm (and, in softplusf,
-// the hardware exponential: relative error ~1e-6, far inside the threshold tolerance). log1p(u) is taken as
+// softplus(x) = max(x, 0) + log1p(u), u = e^{-|x|} in (0, 1], from the hardware exponential and
+// logarithm (relative error ~1e-6, far inside the threshold tolerance). log1p(u) is taken as
 // log(w) u / (w - 1) with w = 1 + u rounded, which cancels the rounding of w (Goldberg, 1991,
 // "What every computer scientist should know about floating-point arithmetic", Theorem 4);
 // when w rounds to 1, log1p(u) = u to working precision.
-__device__ __forceinline__ float softplus_of(float x, float u) {
+__device__ __forceinline__ float softplusf(float x) {
+    const float u = __expf(-fabsf(x));
     const float w = 1.0f + u;
     const float l = (w == 1.0f) ? u : __logf(w) * (u * __builtin_amdgcn_rcpf(w - 1.0f));
     return fmaxf(x, 0.0f) + l;
 }
-__device__ __forceinline__ float softplusf(float x) { return softplus_of(x, __expf(-fabsf(x))); }
 
 // bf16 per staged pixel: an odd multiple of 32 bytes, which puts the 16-byte pieces that a fragment read takes
 // together (4 consecutive pixels of one piece beside 4 others of the next piece) on distinct banks. With 16
@@ -73,13 +73,14 @@ constexpr size_t conv_lds_bytes() {
 
 // 2^(x c) for c given as the float chi and the rest clo, to about an ulp: the rounding error of x chi and the
 // product x clo enter as a factor 1 + ln 2 times their sum (a rounded product alone would cost |x c| / 2 ulp
-// of the result, the rounding of c as much again). Beyond 2^126 it stays there, so that 1 + 2^(x c) has a normal
-// reciprocal; NaN stays NaN.
+// of the result, the rounding of c as much again). RANGE: any x; beyond 2^126 it stays there, so that
+// 1 + 2^(x c) has a normal reciprocal, and NaN stays NaN. Else -126 <= x <= 0.
+template <bool RANGE>
 __device__ __forceinline__ float exp2_product(float x, float chi, float clo) {
     constexpr float LN2 = 0.693147180559945309f;
     const float t = x * chi;
-    const float e = __builtin_amdgcn_exp2f(t > 126.0f ? 126.0f : t);
-    const float lo = fabsf(t) < 126.0f ? fmaf(x, clo, fmaf(x, chi, -t)) : 0.0f;
+    const float e = __builtin_amdgcn_exp2f(RANGE && t > 126.0f ? 126.0f : t);
+    const float lo = !RANGE || fabsf(t) < 126.0f ? fmaf(x, clo, fmaf(x, chi, -t)) : 0.0f;
     return fmaf(e, lo * LN2, e);
 }
 // 1 / w, 1 <= w <= 2^126 + 1: the hardware's reciprocal and one Newton step
@@ -91,13 +92,14 @@ __device__ __forceinline__ float rcp_newton(float w) {
 // The training loss of one coefficient, with o the network's output and z, zc the noisy and clean
 // coefficients in noise units: tau = softplus(o), g = sigmoid((|z| - tau) / T), r = z g - zc; adds r^2 to
 // lsum and gives v = d(loss_scale r^2) / d o = -2 loss_scale / T r z g (1 - g) sigmoid(o). With
-// u = e^-|o| and w = 1 + u, softplus(o) comes from u and sigmoid(o) is 1 / w or u / w, so the three functions of
-// o share one exponential; the division by T is part of the gate's exponent. tau keeps softplus's
-// relative precision for small thresholds too (log w alone loses it: below o = -17 it is 0, and a small
-// temperature magnifies the loss before that). The exponentials are within about an ulp and the
-// reciprocals within one: against 64 bits, g and the gradient are as far off as with the library's expf and IEEE
-// divisions, at 59 VALU instructions instead of 105, which bound the epilogue (205 M values at 16 x 512^2 x
-// 49). The bare hardware functions (20 instructions; a training step 1.99 ms instead of 2.04) put r and the
+// u = e^-|o| and w = 1 + u, softplus(o) = max(o, 0) + log1p(u) and sigmoid(o) is 1 / w or u / w, so the three
+// functions of o share one exponential and one reciprocal; the division by T is part of the gate's
+// exponent. log1p(u) is log w plus what the rounding of w left out, (u - (w - 1)) / w: tau keeps its relative
+// precision for small thresholds (log w alone loses it: below o = -17 it is 0, and a small temperature
+// magnifies the loss before that). The exponentials are within about an ulp and the reciprocals within one:
+// against 64 bits, tau, g and the gradient are no further off than with the library's expf and IEEE
+// divisions, at 42 VALU instructions instead of 105, which bound the epilogue (205 M values at 16 x 512^2 x
+// 49). The bare hardware functions (20 instructions; a training step 1.96 ms instead of 1.98) put r and the
 // gradient about a fifth to a third further off.
 struct GateLoss {
     float ehi, elo;  // log2(e) / T
@@ -105,10 +107,12 @@ struct GateLoss {
 };
 __device__ __forceinline__ void gate_loss(float o, float z, float zc, const GateLoss& gl, float& lsum, float& v) {
     constexpr float L2E = 1.44269504088896341f, L2E_LO = (float)(1.44269504088896340736 - (double)L2E);
-    const float u = exp2_product(-fabsf(o), L2E, L2E_LO);
-    const float tau = softplus_of(o, u);
-    const float so = (o > 0.0f ? 1.0f : u) * rcp_newton(1.0f + u);
-    const float g = rcp_newton(1.0f + exp2_product(tau - fabsf(z), gl.ehi, gl.elo));
+    constexpr float LN2 = 0.693147180559945309f;
+    const float u = exp2_product<false>(fmaxf(-fabsf(o), -126.0f), L2E, L2E_LO);  // (o = NaN reaches tau)
+    const float w = 1.0f + u, rw = rcp_newton(w);
+    const float tau = (o < 0.0f ? 0.0f : o) + fmaf(__builtin_amdgcn_logf(w), LN2, (u - (w - 1.0f)) * rw);
+    const float so = (o < 0.0f ? u : 1.0f) * rw;
+    const float g = rcp_newton(1.0f + exp2_product<true>(tau - fabsf(z), gl.ehi, gl.elo));
     const float r = fmaf(z, g, -zc);
     lsum = fmaf(r, r, lsum);
     v = gl.c * r * (z * g) * (1.0f - g) * so;

@@ -47,3 +47,39 @@ def test_small_thresholds_keep_their_precision(gpu, o):
     print(f"loss rel {abs(loss - L) / L:.2e}, grad b3 rel L2 {eg:.2e}")
     assert abs(loss - L) <= 5e-5 * L
     assert eg <= 3e-3
+
+
+@pytest.mark.parametrize("b3,T,zscale,nan", [(200.0, 0.5, 1.0, False), (-200.0, 0.5, 1.0, False), (1.0, 1e-38, 20.0, False),
+                                             (1.0, 3e38, 1.0, False), (float("nan"), 0.5, 1.0, True),
+                                             (1.0, 0.5, float("nan"), True)])
+def test_gate_at_the_ends_of_its_range(gpu, b3, T, zscale, nan):
+    """Outputs whose exponential underflows, temperatures whose quotient overflows or vanishes, and NaN, which the
+    loss keeps. At 1e-38 the gate is a step (|z| far from tau), at 3e38 it is 1/2 everywhere, with outputs of
+    200 it is closed and with -200 half open at z = 0 only: the loss from FP64 within 5e-5 in each case."""
+    from paper_2006_04591_amd import ShearletSystem, ShrinkNet
+
+    print(f"case: gate range b3={b3} T={T} zscale={zscale}", flush=True)
+    K, N, M = 3, 16, 128
+    rng = np.random.default_rng(7)
+    S = np.fft.fft2(rng.standard_normal((K, N, M)))
+    rms = np.sqrt(np.mean(np.abs(S) ** 2, axis=(1, 2)))
+    z = rng.choice([-1.0, 1.0], (1, K, N, M)) * rng.uniform(2.0, 4.0, (1, K, N, M)) * zscale
+    cn = (z * rms[None, :, None, None]).astype(np.float32)
+    cc = np.nan_to_num(0.5 * cn, nan=1.0).astype(np.float32)
+    p = OS.init_params(K, seed=5)
+    p = OS.ShrinkParams(p.W1, p.b1, p.W2, p.b2, 0.0 * p.W3, np.full(K, b3))
+    to = lambda v: torch.from_numpy(np.ascontiguousarray(v, dtype=np.float32)).to(gpu)  # noqa: E731
+    with ShearletSystem.from_spectra(np.fft.fftshift(S, axes=(1, 2))) as s:
+        net = ShrinkNet(s, {n: getattr(p, n) for n in ShrinkNet.NAMES})
+        loss = float(net.train_step(to(cn), to(cc), torch.ones(1, device=gpu), lr=0.0, temperature=T))
+        torch.cuda.synchronize()
+        gb3 = net.grad("b3")
+    if nan:
+        assert np.isnan(loss)
+        return
+    sc = (1.0 / rms)[None, :, None, None]
+    z64, zc64, tau = cn * sc, cc * sc, OS.softplus(b3)
+    x = np.clip((np.abs(z64) - tau) / T, -1e4, 1e4)
+    want = float(np.mean(((z64 / (1.0 + np.exp(np.clip(-x, -700, 700))) - zc64) ** 2)[:, :-1]))
+    assert abs(loss - want) <= 5e-5 * want
+    assert bool(torch.isfinite(gb3).all())
